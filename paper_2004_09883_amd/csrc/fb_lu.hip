@@ -39,92 +39,55 @@ constexpr int LU_PANEL_THREADS = FB_LU_PANEL_THREADS;
 constexpr int LU_ROWS = (int)(LU_MAX_N / LU_PANEL_THREADS);   // rows of the panel per thread
 static_assert(LU_ROWS * LU_PANEL_THREADS >= LU_MAX_N, "the panel kernel holds every row of a panel");
 
-// ---- pivot search within a wavefront
+// ---- pivot search
 //
 // The pivot is the first row (smallest position) among those of largest
-// magnitude.  It is found in two reductions: the largest magnitude M, then
-// the smallest position among the candidates whose magnitude equals M, so
-// each step is a single max or min instead of a compare-and-select on
-// (magnitude, row) pairs.  Magnitudes are compared as binary64 values, so
-// ties are exact.  The all-reduce over 64 lanes exchanges with the lanes
-// l ^ 1, l ^ 2 (DPP quad permutations), 7 - l within 8 and 15 - l within 16
-// (DPP half-row and row mirrors), then with the same lane of the row r ^ 1
-// and r ^ 2 (permlane16 / permlane32 swaps): each step pairs disjoint halves
-// of a group, so after six steps every lane holds the wave's result.
+// magnitude.  Magnitudes are compared as the integers their binary64 bits
+// are, high words first: the largest high word of a wavefront comes from four
+// DPP maxima within its 16-lane rows (lanes l ^ 1, l ^ 2, 7 - l within 8,
+// 15 - l within 16) and two row broadcasts, and the ballot of the rows that
+// hold it names the candidate.  Only when several rows share it
+// (a uniform branch) do the low words, and among equal magnitudes the
+// positions, decide.  A NaN counts as larger than any number, so a column
+// always has a pivot row.
 template <int CTRL> __device__ __forceinline__ int dpp_i(int x)
 {
     return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, false);
 }
-template <int CTRL> __device__ __forceinline__ double dpp_d(double x)
-{
-    const long long u = __double_as_longlong(x);
-    const int lo = dpp_i<CTRL>((int)u), hi = dpp_i<CTRL>((int)(u >> 32));
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-// the same lane of row r ^ 1 (ROWS = 1) or r ^ 2 (ROWS = 2)
-template <int ROWS> __device__ __forceinline__ int row_partner_i(int x, int lane)
-{
-    if constexpr (ROWS == 1) {
-        const auto r = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
-        return (int)((lane & 16) ? r[0] : r[1]);
-    } else {
-        const auto r = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
-        return (int)((lane & 32) ? r[0] : r[1]);
-    }
-}
-template <int ROWS> __device__ __forceinline__ double row_partner_d(double x, int lane)
-{
-    const long long u = __double_as_longlong(x);
-    const int lo = row_partner_i<ROWS>((int)u, lane), hi = row_partner_i<ROWS>((int)(u >> 32), lane);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-__device__ __forceinline__ double dmax(double x, double y) { return x > y ? x : y; }
+__device__ __forceinline__ int imax(int x, int y) { return x > y ? x : y; }
 __device__ __forceinline__ int imin(int x, int y) { return x < y ? x : y; }
-__device__ __forceinline__ double wave_max(double x, int lane)
+// all lanes of each group of 8 get the group's largest x
+__device__ __forceinline__ int max8(int x)
 {
-    x = dmax(x, dpp_d<0xB1>(x));     // quad_perm [1,0,3,2]: l ^ 1
-    x = dmax(x, dpp_d<0x4E>(x));     // quad_perm [2,3,0,1]: l ^ 2
-    x = dmax(x, dpp_d<0x141>(x));    // row_half_mirror
-    x = dmax(x, dpp_d<0x140>(x));    // row_mirror
-    x = dmax(x, row_partner_d<1>(x, lane));
-    return dmax(x, row_partner_d<2>(x, lane));
+    x = imax(x, dpp_i<0xB1>(x));    // quad_perm [1,0,3,2]: l ^ 1
+    x = imax(x, dpp_i<0x4E>(x));    // quad_perm [2,3,0,1]: l ^ 2
+    return imax(x, dpp_i<0x141>(x));   // row_half_mirror
 }
-__device__ __forceinline__ int wave_min(int i, int lane)
+// the largest x of the wavefront (x >= INT_MIN + 1), as a scalar
+__device__ __forceinline__ int wave_max(int x)
 {
-    i = imin(i, dpp_i<0xB1>(i));
-    i = imin(i, dpp_i<0x4E>(i));
-    i = imin(i, dpp_i<0x141>(i));
-    i = imin(i, dpp_i<0x140>(i));
-    i = imin(i, row_partner_i<1>(i, lane));
-    return imin(i, row_partner_i<2>(i, lane));
+    x = max8(x);
+    x = imax(x, dpp_i<0x140>(x));   // row_mirror
+    // rows 1 and 3 take row 0's and row 2's, then row 3 takes row 1's
+    x = imax(x, __builtin_amdgcn_update_dpp((int)0x80000000, x, 0x142, 0xA, 0xF, false));   // row_bcast15
+    x = imax(x, __builtin_amdgcn_update_dpp((int)0x80000000, x, 0x143, 0xC, 0xF, false));   // row_bcast31
+    return __builtin_amdgcn_readlane(x, 63);
 }
-
-// step S (0 .. 5) of wave_max / wave_min, so that other work can be placed
-// between the steps
-template <int S> __device__ __forceinline__ double wave_max_step(double x, int lane)
+__device__ __forceinline__ int hi_word(double x) { return (int)(__double_as_longlong(x) >> 32); }
+__device__ __forceinline__ int lo_word(double x) { return (int)__double_as_longlong(x); }
+// a low word as an integer whose signed order is the word's unsigned order
+__device__ __forceinline__ int lo_key(int lo) { return lo ^ (int)0x80000000; }
+__device__ __forceinline__ double lane_d(double x, int l)
 {
-    if constexpr (S == 0) return dmax(x, dpp_d<0xB1>(x));
-    else if constexpr (S == 1) return dmax(x, dpp_d<0x4E>(x));
-    else if constexpr (S == 2) return dmax(x, dpp_d<0x141>(x));
-    else if constexpr (S == 3) return dmax(x, dpp_d<0x140>(x));
-    else if constexpr (S == 4) return dmax(x, row_partner_d<1>(x, lane));
-    else return dmax(x, row_partner_d<2>(x, lane));
-}
-template <int S> __device__ __forceinline__ int wave_min_step(int i, int lane)
-{
-    if constexpr (S == 0) return imin(i, dpp_i<0xB1>(i));
-    else if constexpr (S == 1) return imin(i, dpp_i<0x4E>(i));
-    else if constexpr (S == 2) return imin(i, dpp_i<0x141>(i));
-    else if constexpr (S == 3) return imin(i, dpp_i<0x140>(i));
-    else if constexpr (S == 4) return imin(i, row_partner_i<1>(i, lane));
-    else return imin(i, row_partner_i<2>(i, lane));
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)lo_word(x), l);
+    const unsigned hi = __builtin_amdgcn_readlane((unsigned)hi_word(x), l);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-struct PanelCand {
-    double best;
-    int row;
-    int pad;
+// A wave's candidate for the pivot: the magnitude's words and the row's
+// position; hi < 0 when the wave holds no row that can be the pivot.
+struct __attribute__((aligned(16))) PanelCand {
+    int hi, lo, row, pad;
 };
 
 // The factorization of one panel (columns k .. k+nb-1, rows k .. k+m-1)
@@ -132,15 +95,23 @@ struct PanelCand {
 // position in the panel in lab[r] (rows that are not in the panel carry a
 // position >= m).  Rows never move between registers: exchanging rows j and
 // p exchanges two positions, and at the end every row is stored at the
-// position it carries.  Ties between pivot candidates go to the smallest
-// position: the first row of largest magnitude in the exchanged order.
+// position it carries.
 //
-// One barrier per column.  Before it, each wave publishes its candidate
-// (largest magnitude, smallest position of that magnitude) and that
-// candidate's whole row; after it, every wave reduces the W candidates the
-// same way and reads the pivot row.  The buffers alternate with the
-// column's parity: a thread that reaches column j + 1's barrier has finished
-// every read of column j - 1's buffers.
+// What bounds it: the chain of a column (pivot search, publication, barrier,
+// quotients, update of the next column), and with several rows per thread
+// the instructions of the two waves that share a SIMD.  So everything that is
+// the same for a whole wave is kept in scalars: per register slot the lanes
+// whose row has not been a pivot yet are a 64-bit mask (alive[r]) that the
+// updates run under, with no select per element; the candidate is named by
+// scalar bit scans; and after the column's single barrier each lane reads
+// two elements of one of the W candidate rows, the winner among the W
+// candidates is found the same way as within a wave, and the pivot row's
+// elements are read out of the lanes as scalars, so the barrier is followed
+// by one LDS round trip.  Measured against a search by compare-and-select on
+// binary64 values with selects per element: 2048 x 2048 5.34 -> 4.87 ms,
+// 333 x 333 572 -> 455 us (same bits).  The buffers alternate with the column's parity: a
+// thread that reaches column j + 1's barrier has finished every read of
+// column j - 1's buffers.
 //
 // R: the register slots that can hold rows of the panel (slot r holds
 // physical rows t + LU_PANEL_THREADS r, so a panel of m rows needs
@@ -148,14 +119,7 @@ struct PanelCand {
 // shortens every column step of the short panels.
 //
 // FULL: nb == LU_NB (every panel but possibly the last), with no test per
-// column.  The column steps contain no branch apart from the candidate row's
-// publication and the barrier (rows that are not updated keep their values
-// through selects, the pivots are kept in registers and stored at the end),
-// and the reductions of column j + 1 are computed at the end of step j:
-// once column j + 1 is updated, its candidates are reduced over the wave
-// while the rest of step j's update (columns j + 2 ..) is placed between the
-// reduction's dependent steps, whose latency it fills (5.49 -> 5.31 ms for
-// the 2048 x 2048 factorization).
+// column.
 constexpr int LU_W = LU_PANEL_THREADS / 64;   // waves of the panel's workgroup
 struct PanelShared {
     PanelCand cand[2][LU_W];
@@ -168,123 +132,128 @@ __device__ __forceinline__ void panel_columns(double (&v)[LU_ROWS][LU_NB], int (
                                               int32_t *__restrict__ ipiv, int32_t *__restrict__ info, PanelShared &sh)
 {
     constexpr int W = LU_W;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    static_assert(W == 8 && LU_NB == 16, "a wave reads the W candidate rows with one 16-byte access per lane");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (FULL) nb = LU_NB;
     // the first zero pivot and the pivot positions, kept in registers (a
     // global access per column would stall every column's barrier on memory
     // latency) and stored at the end; the first panel starts the record
     int32_t zero_at = k == 0 ? 0 : info[0];
     int piv_at[LU_NB];
-    // pivot candidates of column j: per thread the largest |a[.][j]| among
-    // its rows at positions >= j and the smallest such position
-    double mt = 0.0;
-    int lt = 0, br = 0;
-    auto candidates = [&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        double x[LU_ROWS];
+    uint64_t alive[R];   // lanes whose row r may still be the pivot
 #pragma unroll
-        for (int r = 0; r < R; r++) x[r] = (lab[r] >= j && lab[r] < m) ? fabs(v[r][j]) : -1.0;
-        mt = x[0];
-#pragma unroll
-        for (int r = 1; r < R; r++) mt = dmax(mt, x[r]);
-        lt = 0x7fffffff;
-        br = 0;
-#pragma unroll
-        for (int r = R - 1; r >= 0; r--) {
-            const bool t = x[r] == mt && lab[r] < lt;
-            lt = t ? lab[r] : lt;
-            br = t ? r : br;
-        }
-    };
-    candidates(std::integral_constant<int, 0>{});
-    double mw = wave_max(mt, lane);
-    int pwv = wave_min(mt == mw ? lt : 0x7fffffff, lane);
+    for (int r = 0; r < R; r++) alive[r] = __ballot(lab[r] < m);
 
     static_for<0, LU_NB>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         if (FULL || j < nb) {   // uniform
             constexpr int h = j & 1;
-            // ---- publish the wave's candidate and its row
-            if (lane == 0) sh.cand[h][wave] = PanelCand{mw, pwv, 0};
-            if (lt == pwv) {   // the one lane of the wave that holds the candidate (positions are unique)
+            // ---- the wave's candidate: register slot cr, lane cl
+            int hi[R], best = -1;
 #pragma unroll
-                for (int r = 0; r < R; r++) {
-                    if (br == r) {
+            for (int r = 0; r < R; r++) {
+                hi[r] = __builtin_amdgcn_inverse_ballot_w64(alive[r]) ? (hi_word(v[r][j]) & 0x7fffffff) : -1;
+                best = imax(best, hi[r]);
+            }
+            const int hm = wave_max(best);
+            uint64_t at[R];   // the candidate: one lane of one slot
+            int count = 0;
 #pragma unroll
-                        for (int c = 0; c < LU_NB; c++) sh.crow[h][wave][c] = v[r][c];
-                        asm volatile("" ::: "memory");   // keeps the stores apart (merged, they index v at run time)
-                    }
+            for (int r = 0; r < R; r++) {
+                at[r] = __ballot(hi[r] == hm);
+                count += __popcll(at[r]);
+            }
+            if (__builtin_expect(count != 1, 0)) {
+                if (hm < 0) {   // no row left in this wave
+#pragma unroll
+                    for (int r = 0; r < R; r++) at[r] = 0;
+                    if (lane == 0) sh.cand[h][wave].hi = -1;
+                } else {   // the low words decide, then the positions
+                    int lk = (int)0x80000000, lb = 0x7fffffff;
+#pragma unroll
+                    for (int r = 0; r < R; r++) lk = hi[r] == hm ? imax(lk, lo_key(lo_word(v[r][j]))) : lk;
+                    const int lm = wave_max(lk);
+#pragma unroll
+                    for (int r = 0; r < R; r++)
+                        lb = hi[r] == hm && lo_key(lo_word(v[r][j])) == lm ? imin(lb, lab[r]) : lb;
+                    const int pm = -wave_max(-lb);
+#pragma unroll
+                    for (int r = 0; r < R; r++) at[r] &= __ballot(lab[r] == pm);   // positions are unique
+                }
+            }
+            // ---- its holder publishes it and its row (columns j ..)
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                if (__builtin_amdgcn_inverse_ballot_w64(at[r])) {
+                    sh.cand[h][wave] = PanelCand{hi[r], lo_word(v[r][j]), lab[r], 0};
+#pragma unroll
+                    for (int c = j; c < LU_NB; c++) sh.crow[h][wave][c] = v[r][c];
+                    asm volatile("" ::: "memory");   // keeps the slots apart (merged, they index v at run time)
                 }
             }
             __syncthreads();
-            // ---- the pivot: the same two reductions over the W wave
-            // candidates, lane l reading candidate l mod W
-            static_assert(W == 8, "the candidates are reduced within groups of 8 lanes");
-            const PanelCand cl = sh.cand[h][lane & (W - 1)];
-            double b = cl.best;
-            b = dmax(b, dpp_d<0xB1>(b));
-            b = dmax(b, dpp_d<0x4E>(b));
-            b = dmax(b, dpp_d<0x141>(b));
-            int p = b == cl.best ? cl.row : 0x7fffffff;
-            p = imin(p, dpp_i<0xB1>(p));
-            p = imin(p, dpp_i<0x4E>(p));
-            p = imin(p, dpp_i<0x141>(p));
-            const int pw = __ffsll((long long)(__ballot(lane < W && cl.row == p) & 0xffull)) - 1;
+            // ---- the pivot: lane l reads candidate l mod W and two elements
+            // of its row
+            const PanelCand c8 = sh.cand[h][lane & (W - 1)];
+            const double2 e = *reinterpret_cast<const double2 *>(&sh.crow[h][lane & (W - 1)][2 * (lane >> 3)]);
+            const int ph = max8(c8.hi);
+            uint64_t win = __ballot(c8.hi == ph) & 0xffull;
+            if (__builtin_expect(__popcll(win) > 1, 0)) {
+                const bool t = c8.hi == ph;
+                const int lm = max8(t ? lo_key(c8.lo) : (int)0x80000000);
+                const bool u = t && lo_key(c8.lo) == lm;
+                const int pm = -max8(u ? -c8.row : -0x7fffffff);
+                win = __ballot(u && c8.row == pm) & 0xffull;
+            }
+            const int pw = __ffsll((long long)win) - 1;
+            const int p = __builtin_amdgcn_readlane(c8.row, pw);
             piv_at[j] = p;
-            zero_at = (b == 0.0 && zero_at == 0) ? (int32_t)(k + j + 1) : zero_at;
-            const double *rowp = sh.crow[h][pw];
             double pr[LU_NB];
 #pragma unroll
-            for (int c = j; c < LU_NB; c++) pr[c] = rowp[c];
-#pragma unroll
-            for (int r = 0; r < R; r++) lab[r] = lab[r] == j ? p : (lab[r] == p ? j : lab[r]);
-            // ---- scale the column below the pivot (a zero pivot scales
-            // nothing); rows that are not updated keep their values
+            for (int c = j; c < LU_NB; c++) pr[c] = lane_d((c & 1) ? e.y : e.x, pw + 8 * (c >> 1));
             const double piv = pr[j];
-            bool up[LU_ROWS];
-            double l[LU_ROWS];
+            // ---- exchange the positions j and p; the pivot row is done
 #pragma unroll
             for (int r = 0; r < R; r++) {
-                up[r] = lab[r] > j && lab[r] < m && piv != 0.0;
-                const double q = v[r][j] / piv;
-                l[r] = q;
-                v[r][j] = up[r] ? q : v[r][j];
+                const bool t = lab[r] == p;
+                alive[r] &= ~__ballot(t);
+                lab[r] = t ? j : (lab[r] == j ? p : lab[r]);
             }
-            auto update = [&](auto cc) {
-                constexpr int c = decltype(cc)::value;
-                if constexpr (c < LU_NB) {
+            if (__builtin_expect(piv == 0.0, 0)) {   // uniform; a zero pivot scales nothing
+                zero_at = zero_at == 0 ? (int32_t)(k + j + 1) : zero_at;
+            } else {
+                // ---- scale the column below the pivot.  |v| <= |piv|, so
+                // where piv is far from the ends of the exponent range the
+                // quotients are the reciprocal's product corrected by one
+                // residual, as in Markstein, "Computation of elementary
+                // functions on the IBM RISC System/6000 processor" (1990);
+                // the reciprocal is shared by the rows
+                const int ex = (hi_word(piv) >> 20) & 0x7ff;
+                double l[R];
+                if (__builtin_expect(ex > 1023 - 400 && ex < 1023 + 400, 1)) {
+                    double rc = __builtin_amdgcn_rcp(piv);
+                    rc = fma(fma(-piv, rc, 1.0), rc, rc);
+                    rc = fma(fma(-piv, rc, 1.0), rc, rc);
+                    rc = fma(fma(-piv, rc, 1.0), rc, rc);
 #pragma unroll
                     for (int r = 0; r < R; r++) {
-                        v[r][c] = up[r] ? v[r][c] - l[r] * pr[c] : v[r][c];
-                        // computed here, not sunk to its first use (the
-                        // next column's publication)
-                        asm volatile("" : "+v"(v[r][c]));
+                        const double q = v[r][j] * rc;
+                        l[r] = fma(fma(-piv, q, v[r][j]), rc, q);
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < R; r++) l[r] = v[r][j] / piv;
+                }
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    if (__builtin_amdgcn_inverse_ballot_w64(alive[r])) {
+                        asm volatile("" : "+v"(l[r]));   // a masked region, not a select per element
+                        v[r][j] = l[r];
+#pragma unroll
+                        for (int c = j + 1; c < LU_NB; c++) v[r][c] = fma(-l[r], pr[c], v[r][c]);
                     }
                 }
-            };
-            if constexpr (j + 1 < LU_NB) {
-                // ---- column j + 1 first, then its candidates and their
-                // reductions, with columns j + 2 .. between the steps
-                update(std::integral_constant<int, j + 1>{});
-                candidates(std::integral_constant<int, j + 1>{});
-                double mwn = mt;
-                static_for<0, 6>([&](auto sc) {
-                    constexpr int st = decltype(sc)::value;
-                    mwn = wave_max_step<st>(mwn, lane);
-                    update(std::integral_constant<int, j + 2 + st>{});
-                    __builtin_amdgcn_sched_barrier(0);   // keep the pairs apart: the scheduler would bunch them
-                });
-                int pwn = mt == mwn ? lt : 0x7fffffff;
-                static_for<0, 6>([&](auto sc) {
-                    constexpr int st = decltype(sc)::value;
-                    pwn = wave_min_step<st>(pwn, lane);
-                    update(std::integral_constant<int, j + 8 + st>{});
-                    __builtin_amdgcn_sched_barrier(0);
-                });
-                update(std::integral_constant<int, j + 14>{});
-                update(std::integral_constant<int, j + 15>{});
-                mw = mwn;
-                pwv = pwn;
             }
         }
     });
@@ -304,6 +273,7 @@ __device__ __forceinline__ void panel_columns(double (&v)[LU_ROWS][LU_NB], int (
         info[0] = zero_at;
     }
 }
+
 // The first panel (and, with the lookahead off, every panel): rows k ..
 // n-1 of columns k .. k+nb-1 loaded into registers, then factored.
 template <bool FULL, int R>

@@ -97,3 +97,57 @@ def test_lu_rejects_bad_arguments():
     assert e.value.code == fb.FB_ERR_UNSUPPORTED_SIZE
     with pytest.raises(fb.FbError):
         fb.fb_lu_factor(torch.zeros((8, 8), dtype=torch.float64, device="cuda"), ipiv[:4], info)
+
+
+def tie_matrix(n, kind, seed):
+    """Blocks of 4 (kind "equal": 4 x 4 matrices of +-1, exact in every
+    elimination order) or of 2 ("low": pivots that differ in the last bits of
+    the mantissa only, or not at all) on the diagonal, the rows shuffled."""
+    rng = np.random.default_rng(seed)
+    a = np.eye(n)
+    if kind == "equal":
+        h = np.array([[1, 1, 1, 1], [1, -1, 1, -1], [1, 1, -1, -1], [1, -1, -1, 1]], dtype=np.float64)
+        for k in range(0, n - 3, 4):
+            a[k:k + 4, k:k + 4] = h * rng.choice([-1.0, 1.0], 4)[:, None]
+    else:
+        for k in range(0, n - 1, 2):
+            s = (1.0 + rng.integers(0, 3, 2) * 2.0**-52) * rng.choice([-1.0, 1.0], 2)
+            a[k:k + 2, k:k + 2] = [[s[0], 1.0], [s[1], -s[0] * s[1] / abs(s[0] * s[1])]]
+    return a[rng.permutation(n)]
+
+
+@pytest.mark.parametrize("kind", ["equal", "low"])
+@pytest.mark.parametrize("n", [4, 63, 66, 512, 530, 1040, 2048])
+def test_lu_pivot_ties_take_the_first_row(n, kind):
+    """Candidates of equal magnitude, or equal in the high word, in different
+    lanes, waves and register slots: the oracle's pivots exactly."""
+    print(f"lu ties n={n} {kind}", flush=True)
+    a = tie_matrix(n, kind, n)
+    lu, ipiv, info, _ = gpu_lu(a)
+    lu_ref, ipiv_ref, info_ref = oracle.lu(a)
+    assert info == info_ref == 0
+    assert np.array_equal(ipiv, ipiv_ref)
+    assert np.max(np.abs(lu - lu_ref)) <= 1e-11 * np.max(np.abs(lu_ref))
+
+
+@pytest.mark.parametrize("e", [-900, -401, -399, 399, 401, 900])
+def test_lu_column_scales(e):
+    """Columns scaled by powers of two on both sides of the exponent range
+    in which quotients come from the pivot's reciprocal: the same pivots and
+    L, U scaled."""
+    n = 150
+    a = np.random.default_rng(9).uniform(-1, 1, (n, n))
+    d = np.where(np.arange(n) % 3 == 1, 2.0**e, 1.0)
+    lu, ipiv, info, _ = gpu_lu(a * d)
+    lu_ref, ipiv_ref, _ = oracle.lu(a)
+    assert info == 0 and np.array_equal(ipiv, ipiv_ref)
+    lu = np.tril(lu, -1) + np.triu(lu) / d
+    assert np.max(np.abs(lu - lu_ref)) <= 1e-11 * np.max(np.abs(lu_ref))
+
+
+def test_lu_nan_and_inf_end_with_rows_of_the_matrix_as_pivots():
+    for bad in (np.nan, np.inf):
+        a = np.random.default_rng(2).uniform(-1, 1, (70, 70))
+        a[40, 3] = bad
+        _, ipiv, info, _ = gpu_lu(a)
+        assert info == 0 and np.all(ipiv >= np.arange(70)) and np.all(ipiv < 70)
