@@ -45,10 +45,11 @@ template <typename V, int N, bool CONTIG, bool MX = false> struct PassCfg {
     static constexpr bool SPLIT = FB_SPLIT_EXCHANGE && std::is_same<V, double2>::value && N <= FB_SPLIT_MAX_N;
     using LdsT = typename std::conditional<SPLIT, double, V>::type;   // LDS element
     static constexpr RadixPlan RP = radix_plan(N);
-    static constexpr int T = threads_per_pencil(N);
+    static constexpr GroupPlan GP = group_plan(N, grouped(N, CONTIG, MX));
+    static constexpr int T = GP.threads;
     static constexpr int P = pencils_per_wg(N, CONTIG, (int)sizeof(V), MX, SPLIT);
     static constexpr int THREADS = P * T;
-    static constexpr int M = regs_per_thread(N);
+    static constexpr int M = GP.elems;
     static constexpr int LS = lds_pencil_stride(N);
     static_assert(RP.count >= 1, "pass needs at least one stage");
 };
@@ -313,6 +314,55 @@ struct MxGlobalOut {
     }
 };
 
+// Element I of a group's butterfly (mixed radix, the first stage's digit
+// most significant) lands group_out(I) beyond the butterfly's first output;
+// over the first `cnt` stages only, the same sum is what a later stage's
+// twiddle index gains.
+constexpr int group_out(const RadixPlan &rp, int first, int cnt, int I)
+{
+    int off = 0;
+    for (int t = cnt - 1; t >= 0; t--) {
+        off += (I % rp.r[first + t]) * rp.ns[first + t];
+        I /= rp.r[first + t];
+    }
+    return off;
+}
+
+// The stages of group S on butterfly b, whose G elements are in w[0 .. G):
+// stage by stage, the twiddles and the small DFTs.  After stage t the element
+// of digits (q_0 .. q_t) and remaining input index j is at
+// w[(q_0 .. q_t) G_(t+1) + j].
+template <typename Cfg, int S, typename V> __device__ __forceinline__ void group_butterfly(V *w, int b, const tw_t<V> *tw)
+{
+    constexpr RadixPlan RP = Cfg::RP;
+    constexpr GroupPlan GP = Cfg::GP;
+    constexpr int first = GP.first[S], G = GP.g[S];
+    const int k = b % GP.ns[S];
+    static_for<0, GP.nst[S]>([&](auto tc) {
+        constexpr int t = decltype(tc)::value, s = first + t;
+        constexpr int R = RP.r[s], Ns = RP.ns[s];
+        constexpr int NQ = Ns / GP.ns[S];    // combinations of the earlier digits
+        constexpr int GN = G / (NQ * R);     // elements per digit combination after this stage
+        static_for<0, NQ>([&](auto qc) {
+            constexpr int Q = decltype(qc)::value;
+            constexpr int kq = group_out(RP, first, t, Q);
+#pragma unroll
+            for (int j = 0; j < GN; j++) {
+                V a[R];
+#pragma unroll
+                for (int q = 0; q < R; q++) a[q] = w[Q * R * GN + q * GN + j];
+                if constexpr (Ns > 1) {
+#pragma unroll
+                    for (int q = 1; q < R; q++) a[q] = cmul(a[q], tw[RP.twoff[s] + (q - 1) * Ns + k + kq]);
+                }
+                dft<R>(a);
+#pragma unroll
+                for (int q = 0; q < R; q++) w[Q * R * GN + q * GN + j] = a[q];
+            }
+        });
+    });
+}
+
 // Tile-contiguous output of a strided vector-unit pass (PassArgs::otile):
 // the last stage's outputs go to LDS in natural order, then the workgroup
 // writes the tile's block of P x N elements with consecutive threads on
@@ -392,8 +442,10 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
     using Cfg = PassCfg<V, N, CONTIG, MX>;
     using R = real_t<V>;
     constexpr RadixPlan RP = Cfg::RP;
+    constexpr GroupPlan GP = Cfg::GP;
     constexpr int T = Cfg::T, P = Cfg::P, M = Cfg::M, LS = Cfg::LS;
-    constexpr int NST = RP.count;
+    constexpr int NST = GP.count;   // stage groups: single stages but for repeated radix-3 stages
+    static_assert(!MX || NST == RP.count, "matrix-core passes work stage by stage");
     static_assert(!MX || mx_capable<V, N, CONTIG>(), "no matrix-core variant for this pass");
     constexpr bool PAIR = std::is_same<V, c2x>::value;   // each unit is two adjacent pencils
     static_assert(!PAIR || !CONTIG, "pencil pairs are for strided passes");
@@ -431,7 +483,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
     // first / last matrix-core stage works on the registers
     constexpr bool MX_RIN = MXS::at(0) && MXS::regs();
     constexpr bool MX_ROUT = MXS::at(NST - 1) && MXS::regs_out();
-    constexpr int R0 = RP.r[0];
+    constexpr int R0 = GP.g[0];
     constexpr int NBF0 = N / R0;
     constexpr int U0 = (NBF0 + T - 1) / T;
 
@@ -558,8 +610,8 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
 
     static_for<0, NST>([&](auto sc) {
         constexpr int s = decltype(sc)::value;
-        constexpr int Rr = RP.r[s];
-        constexpr int Ns = RP.ns[s];
+        constexpr int Rr = GP.g[s];
+        constexpr int Ns = GP.ns[s];
         constexpr int NBF = N / Rr;
         constexpr int U = (NBF + T - 1) / T;
 
@@ -666,8 +718,8 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                 // of reals: real parts, then imaginary parts (a round's reads
                 // change only its own part of v, so the other part still holds
                 // the previous stage's outputs for the next round's writes)
-                constexpr int Rp = RP.r[s - 1];
-                constexpr int Nsp = RP.ns[s - 1];
+                constexpr int Rp = GP.g[s - 1];
+                constexpr int Nsp = GP.ns[s - 1];
                 constexpr int NBFp = N / Rp;
                 constexpr int Up = (NBFp + T - 1) / T;
                 R *rrow = (R *)lds + (active ? pp : 0) * LS;
@@ -680,7 +732,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                             const int idx = (b / Nsp) * Nsp * Rp + (b % Nsp);
 #pragma unroll
                             for (int q = 0; q < Rp; q++)
-                                rrow[lds_pos(idx + q * Nsp)] = part ? v[u * Rp + q].y : v[u * Rp + q].x;
+                                rrow[lds_pos(idx + group_out(RP, GP.first[s - 1], GP.nst[s - 1], q))] = part ? v[u * Rp + q].y : v[u * Rp + q].x;
                         }
                     }
                     __syncthreads();
@@ -701,8 +753,8 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
             } else if constexpr (s > 0) {
                 if constexpr (!MxStage<V, N, CONTIG, MX>::at(s - 1)) {
                     // exchange: write the previous stage's outputs
-                    constexpr int Rp = RP.r[s - 1];
-                    constexpr int Nsp = RP.ns[s - 1];
+                    constexpr int Rp = GP.g[s - 1];
+                    constexpr int Nsp = GP.ns[s - 1];
                     constexpr int NBFp = N / Rp;
                     constexpr int Up = (NBFp + T - 1) / T;
 #pragma unroll
@@ -711,7 +763,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                         if (NBFp % T == 0 || b < NBFp) {
                             const int idx = (b / Nsp) * Nsp * Rp + (b % Nsp);
 #pragma unroll
-                            for (int q = 0; q < Rp; q++) row[lds_pos(idx + q * Nsp)] = v[u * Rp + q];
+                            for (int q = 0; q < Rp; q++) row[lds_pos(idx + group_out(RP, GP.first[s - 1], GP.nst[s - 1], q))] = v[u * Rp + q];
                         }
                     }
                     __syncthreads();
@@ -731,22 +783,14 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
 #pragma unroll
             for (int u = 0; active && u < U; u++) {
                 const int b = t + T * u;
-                if (NBF % T == 0 || b < NBF) {
-                    V *w = v + u * Rr;
-                    if constexpr (Ns > 1) {
-                        const int k = b % Ns;
-#pragma unroll
-                        for (int q = 1; q < Rr; q++) w[q] = cmul(w[q], tw[RP.twoff[s] + (q - 1) * Ns + k]);
-                    }
-                    dft<Rr>(w);
-                }
+                if (NBF % T == 0 || b < NBF) group_butterfly<Cfg, s>(v + u * Rr, b, tw);
             }
         }
     });
 
     // ---- last stage output: global stores, pattern b + q N/R
     {
-        constexpr int RL = RP.r[NST - 1];
+        constexpr int RL = GP.g[NST - 1];
         constexpr int NBF = N / RL;
         constexpr int U = (NBF + T - 1) / T;
         if constexpr (MXS::at(NST - 1) && !MX_OUT && !MX_ROUT) {
@@ -760,7 +804,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                 }
             }
         }
-        if constexpr (!CONTIG && !MX && !Cfg::SPLIT) {
+        if constexpr (!CONTIG && !MX && !Cfg::SPLIT && NST == RP.count) {
             if (a.otile) {   // uniform over the workgroup
                 store_tile_contiguous<V, N, CONTIG, NT>(a, tile, tid, active, valid, t, row, lds, v);
                 return;
@@ -776,17 +820,18 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                 if (NBF % T == 0 || b < NBF) {
 #pragma unroll
                     for (int q = 0; q < RL; q++) {
+                        const int pos = b + group_out(RP, GP.first[NST - 1], GP.nst[NST - 1], q);
                         V o = v[u * RL + q];
                         if (a.inv) o = cconj(o);
                         if (a.scale != 1.0) o = cscale(o, sc);
                         if constexpr (PAIR) {
                             if (a.opair_step) {   // the pair's outputs are not adjacent
-                                st_stream<NTA>(go + (int64_t)(b + q * NBF) * OS, o.a);
-                                st_stream<NTA>(go + (int64_t)(b + q * NBF) * OS + a.opair_step, o.b);
+                                st_stream<NTA>(go + (int64_t)pos * OS, o.a);
+                                st_stream<NTA>(go + (int64_t)pos * OS + a.opair_step, o.b);
                                 continue;
                             }
                         }
-                        st_v<NTA, V>(go + (int64_t)(b + q * NBF) * OS, o);
+                        st_v<NTA, V>(go + (int64_t)pos * OS, o);
                     }
                 }
             }

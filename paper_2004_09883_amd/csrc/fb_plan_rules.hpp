@@ -63,20 +63,111 @@ constexpr bool supported_length_b1(int64_t n)
 // Threads that cooperate on one pencil: each holds about 16 elements (n/16
 // threads when 16 divides n; one thread for the short lengths up to 32;
 // otherwise ceil(n/16), and the stages whose butterfly count is not a
-// multiple of it leave the last round part-filled).
+// multiple of it leave the last round part-filled).  Lengths with repeated
+// radix-3 stages take the count of their stage groups instead (group_plan).
 constexpr int threads_per_pencil(int n) { return (n % 16 == 0) ? n / 16 : n <= 32 ? 1 : (n + 15) / 16; }
 
-// Largest number of elements one thread holds over all stages.
-constexpr int regs_per_thread(int n)
+// Whether a pass works its stages in groups (group_plan): the lengths whose
+// radix list repeats the radix 3, on the vector units.  Short contiguous
+// passes would leave a pencil one or two threads, whose loads then lie a
+// pencil apart (27 points: 37 us stage by stage on two threads, 59 us as one
+// group on one thread); they keep single stages.
+constexpr bool grouped(int n, bool contig, bool mx) { return n % 9 == 0 && !mx && (!contig || n >= 81); }
+
+// Stages worked together in registers.  A group of consecutive stages of
+// radices R_s .. R_e and product G is a set of N/G independent butterflies of
+// G elements (butterfly b reads x[b + g N/G], g < G), so a thread that holds
+// those G elements runs all the group's stages without an exchange; the
+// operations and their order on every element are the stages' own.
+//
+// Why: with one group per stage, 216 = 3,3,3,8 makes three LDS exchanges of
+// three- or eight-element butterflies; as (3,3),(3,8) it makes one.  The
+// groups are the fewest whose products, and whose elements per thread, stay
+// within 27 (108 registers of complex128 or of a complex64 pair); among the
+// splits of that many groups the rule takes one that wastes at most a fifth of
+// the lanes' work, if it can with whole rounds of loads (a part-filled round
+// is a branch, and its loads wait behind the others: 216 points on 9 threads,
+// 24 butterflies in 3 rounds, took 31 us where 12 threads take 23), and then
+// the one nearest 18 elements per thread.  One group per stage (fuse = false)
+// everywhere else: the lengths 2^a and 3 2^a exchange between radix-16 stages,
+// and matrix-core stages work on one stage at a time.
+//
+// Measured on 64 MiB complex128 grids against one group per stage, same bits:
+// strided 81 points 21.9 -> 14.3 us, 144: 20.8 -> 14.5, 216: 29.3 -> 22.6,
+// 1458: 35.7 -> 25.3; contiguous 162: 26.2 -> 18.3; complex64 contiguous 729
+// (32 MiB): 20.0 -> 11.7.
+constexpr int kMaxGroupElems = 27;
+constexpr int kGoodGroupElems = 18;
+struct GroupPlan {
+    int count;
+    int first[16];  // first stage of the group
+    int nst[16];    // stages of the group
+    int g[16];      // product of their radices
+    int ns[16];     // product of the radices before the group
+    int threads;    // threads per pencil
+    int elems;      // largest number of elements one thread holds
+};
+
+constexpr GroupPlan groups_of_mask(const RadixPlan &rp, unsigned mask)   // bit i: a group ends after stage i
 {
-    RadixPlan p = radix_plan(n);
-    int T = threads_per_pencil(n), M = 0;
-    for (int s = 0; s < p.count; s++) {
-        int nbf = n / p.r[s];
-        int u = (nbf + T - 1) / T;
-        if (u * p.r[s] > M) M = u * p.r[s];
+    GroupPlan p{};
+    p.count = 0;
+    for (int s = 0; s < rp.count; s++) {
+        if (s == 0 || (mask >> (s - 1) & 1)) {
+            p.first[p.count] = s;
+            p.nst[p.count] = 0;
+            p.g[p.count] = 1;
+            p.ns[p.count] = rp.ns[s];
+            p.count++;
+        }
+        p.nst[p.count - 1]++;
+        p.g[p.count - 1] *= rp.r[s];
     }
-    return M;
+    return p;
+}
+
+constexpr GroupPlan group_plan(int n, bool fuse)
+{
+    const RadixPlan rp = radix_plan(n);
+    GroupPlan best = groups_of_mask(rp, ~0u);
+    best.threads = threads_per_pencil(n);
+    for (int i = 0; i < best.count; i++) {
+        const int u = (n / best.g[i] + best.threads - 1) / best.threads;
+        if (u * best.g[i] > best.elems) best.elems = u * best.g[i];
+    }
+    if (!fuse) return best;
+    best.threads = 0;
+    int best_key[4] = {0, 0, 0, 0};
+    for (unsigned mask = 0; mask < (1u << (rp.count - 1)); mask++) {
+        GroupPlan p = groups_of_mask(rp, mask);
+        bool fits = true;
+        for (int i = 0; i < p.count; i++) fits = fits && p.g[i] <= kMaxGroupElems;
+        if (!fits || (best.threads && p.count > best.count)) continue;
+        for (int t = (n + kMaxGroupElems - 1) / kMaxGroupElems; t <= n / 2 || t == 1; t++) {
+            int elems = 0, work = 0;
+            for (int i = 0; i < p.count; i++) {
+                const int u = (n / p.g[i] + t - 1) / t;
+                if (u * p.g[i] > elems) elems = u * p.g[i];
+                work += u * p.g[i] * t;
+            }
+            if (elems > kMaxGroupElems) continue;
+            const int waste = work / p.count * 1000 / n - 1000;   // per mille
+            const int ragged = (n / p.g[0]) % t != 0 && n / p.g[0] > t ? 1 : 0;
+            const int off = elems > kGoodGroupElems ? elems - kGoodGroupElems : kGoodGroupElems - elems;
+            // in this order: few wasted lanes, distance, all wasted lanes, more threads
+            const int key[4] = {waste > 200 ? waste : ragged, off, waste, -t};
+            if (best.threads && p.count == best.count) {
+                int c = 0;
+                while (c < 3 && key[c] == best_key[c]) c++;
+                if (key[c] >= best_key[c]) continue;
+            }
+            p.threads = t;
+            p.elems = elems;
+            best = p;
+            for (int c = 0; c < 4; c++) best_key[c] = key[c];
+        }
+    }
+    return best;
 }
 
 // LDS row of one pencil: one pad element every 16 (breaks the stride-R
@@ -171,8 +262,35 @@ constexpr int pencils_per_wg_b(int n, bool contig, int esize, bool mx, bool spli
     while (P > 1 && !pencils_fit(P, n, contig, esize, mx, split)) P /= 2;
     return P;
 }
+// Pencils per workgroup of a pass with stage groups, whose thread counts are
+// odd: the count that leaves the fewest lanes of the tile's last wavefront
+// idle, within the LDS budget and 256 (contiguous) or 512 threads.  Strided
+// tiles keep whole 128-byte row segments, two of them where that fits (as
+// the other strided passes, which lose a tenth with one).
+constexpr int grouped_pencils(int n, int threads, bool contig, int esize, bool split)
+{
+    const int elem = split ? 8 : esize;
+    const int budget = (contig ? 20 : split ? FB_LDS_SPLIT_STRIDED_KB : FB_LDS_STRIDED_KB) * 1024;
+    const int max_threads = contig ? 256 : 512;
+    for (int step = contig ? 1 : 256 / esize; step >= 1; step /= 2) {
+        int best = 0, best_idle = 0;   // idle lanes per mille
+        for (int p = step; p * threads <= max_threads && p * lds_pencil_stride(n) * elem <= budget;
+             p += contig ? 1 : 128 / esize) {
+            const int lanes = (p * threads + 63) / 64 * 64;
+            const int idle = (lanes - p * threads) * 1000 / lanes / 20 * 20;
+            if (best == 0 || idle < best_idle) {
+                best = p;
+                best_idle = idle;
+            }
+        }
+        if (best) return best;
+    }
+    return 1;
+}
+
 constexpr int pencils_per_wg(int n, bool contig, int esize, bool mx = false, bool split = false)
 {
+    if (grouped(n, contig, mx)) return grouped_pencils(n, group_plan(n, true).threads, contig, esize, split);
     if (mx) {
         const int P = pencils_per_wg_b(n, contig, esize, true, split);
         if ((P * threads_per_pencil(n)) % 64 == 0) return P;

@@ -112,6 +112,27 @@ def test_fft3d_in_place_equals_out_of_place(dtype):
     assert rel_l2(a, ref) < TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("shape", [(1, 27, 162), (9, 3, 216), (3, 9, 81), (3, 144, 9), (2, 108, 18), (243, 3, 27),
+                                   (216, 1, 27), (54, 9, 3), (1458, 1, 3), (1, 648, 8)])
+def test_grouped_stages_part_filled_tiles(shape, dtype):
+    """Lengths whose radix-3 stages are worked together in registers, with
+    pencil counts that end inside a tile, on each axis: both directions, and
+    the shared first pass of several steps."""
+    print(f"grouped shape={shape} dtype={dtype}", flush=True)
+    for direction in (fb.FB_FORWARD, fb.FB_INVERSE):
+        got, ref = run_fft(shape, dtype, seed=11, direction=direction)
+        assert rel_l2(got, ref) < TOL[dtype], direction
+    plan = fb.Plan(*shape, dtype)
+    u = dev(inputs.uniform_grid(shape, 12), dtype)
+    multi = torch.full((3,) + shape, 3.0, dtype=plan.torch_dtype, device="cuda")
+    one = torch.empty(shape, dtype=plan.torch_dtype, device="cuda")
+    fb.fb_spectral_steps(plan, u, multi, 1e-4, [1.0, 2.0, 3.0])
+    for j in range(3):
+        fb.fb_spectral_step(plan, u, one, 1e-4, j + 1.0)
+        assert torch.equal(one, multi[j]), j
+
+
 def test_round_trip_c128():
     shape = (64, 32, 96)
     x = inputs.uniform_grid(shape, 5)
