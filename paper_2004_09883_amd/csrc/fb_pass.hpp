@@ -51,6 +51,15 @@ template <typename V, int N, bool CONTIG, bool MX = false> struct PassCfg {
     static constexpr int THREADS = P * T;
     static constexpr int M = GP.elems;
     static constexpr int LS = lds_pencil_stride(N);
+    // whether a contiguous tile moves as one block (block_to_rows), with
+    // cached accesses and with non-temporal ones
+    static constexpr bool block(bool nt)
+    {
+        constexpr int seg = T * (int)sizeof(V);   // bytes of a pencil that its threads access together
+        if (!CONTIG || MX) return false;
+        return nt ? N < 512 && seg % 128 != 0 && (seg < 128 || N % 9 == 0 || !SPLIT) : N <= 48;
+    }
+    static constexpr int LIN = (N + T - 1) / T;   // elements per thread of a tile moved as one block
     static_assert(RP.count >= 1, "pass needs at least one stage");
 };
 
@@ -426,6 +435,92 @@ __device__ __forceinline__ void store_tile_contiguous(const PassArgs &a, int64_t
     }
 }
 
+// A contiguous tile moved as one block: P pencils back to back are P x N
+// consecutive elements, which consecutive threads load and store, and which
+// reach the butterflies' threads through the tile's LDS rows (real and
+// imaginary parts in two rounds where the exchanges do so).  Without it, T
+// threads of a pencil read T consecutive elements and the next T threads a
+// pencil further on, so that an access ends inside a cache line, and with
+// non-temporal accesses such lines are fetched again.  Bound: HBM; the LDS
+// round trips are the price.
+//
+// Measured, pencil-wise -> as a block, us.  Non-temporal, grids above 192 MiB:
+// complex128 48 points 154 -> 70, 81: 210 -> 116, 162: 249 -> 122, 243: 405 ->
+// 193, 324: 164 -> 136; complex64 96: 189 -> 75, 128: 116 -> 90, 216: 231 ->
+// 90, 432: 96 -> 84.  Longer passes hold one or two pencils per tile and lose
+// (729 complex128 163 -> 227, 1944 complex64 121 -> 135), and so does a
+// two-round exchange whose accesses pass a line anyway (192 complex128 148 ->
+// 153).  Cached, 64 and 32 MiB: complex128 16 points 33 -> 21, 27: 37 -> 28,
+// 48: 21 -> 21; complex64 16: 31 -> 12, 24: 25 -> 12, 48: 15 -> 12; from 64
+// points on the caches join the accesses and the round trips cost (complex128
+// 64: 19.6 -> 22.1, complex64 96: 13.0 -> 14.2).
+template <typename Cfg, int N, typename V, typename LdsT, int M>
+__device__ __forceinline__ void block_to_rows(const V (&lin)[Cfg::LIN], V (&v)[M], int tid, int t, LdsT *lds, LdsT *row)
+{
+    constexpr int G0 = Cfg::GP.g[0], NBF = N / G0, U = (NBF + Cfg::T - 1) / Cfg::T;
+    static_for<0, Cfg::SPLIT ? 2 : 1>([&](auto hc) {
+        constexpr int part = decltype(hc)::value;
+#pragma unroll
+        for (int i = 0; i < Cfg::LIN; i++) {
+            const int e = tid + i * Cfg::THREADS;
+            if ((Cfg::P * N) % Cfg::THREADS == 0 || e < Cfg::P * N) {
+                LdsT &x = lds[(e / N) * Cfg::LS + lds_pos(e % N)];
+                if constexpr (Cfg::SPLIT) x = part ? lin[i].y : lin[i].x;
+                else x = lin[i];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int b = t + Cfg::T * u;
+            if (NBF % Cfg::T == 0 || b < NBF) {
+#pragma unroll
+                for (int q = 0; q < G0; q++) {
+                    if constexpr (!Cfg::SPLIT) v[u * G0 + q] = row[lds_pos(b + q * NBF)];
+                    else if constexpr (part) v[u * G0 + q].y = row[lds_pos(b + q * NBF)];
+                    else v[u * G0 + q].x = row[lds_pos(b + q * NBF)];
+                }
+            }
+        }
+        __syncthreads();
+    });
+}
+// ... and back: the last group's outputs in v to the block order in lin.  On
+// entry the LDS rows are free.
+template <typename Cfg, int N, typename V, typename LdsT, int M>
+__device__ __forceinline__ void rows_to_block(const V (&v)[M], V (&lin)[Cfg::LIN], int tid, int t, LdsT *lds, LdsT *row)
+{
+    constexpr int L = Cfg::GP.count - 1;
+    constexpr int GL = Cfg::GP.g[L], NBF = N / GL, U = (NBF + Cfg::T - 1) / Cfg::T;
+    static_for<0, Cfg::SPLIT ? 2 : 1>([&](auto hc) {
+        constexpr int part = decltype(hc)::value;
+        if (part) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int b = t + Cfg::T * u;
+            if (NBF % Cfg::T == 0 || b < NBF) {
+#pragma unroll
+                for (int q = 0; q < GL; q++) {
+                    LdsT &x = row[lds_pos(b + group_out(Cfg::RP, Cfg::GP.first[L], Cfg::GP.nst[L], q))];
+                    if constexpr (Cfg::SPLIT) x = part ? v[u * GL + q].y : v[u * GL + q].x;
+                    else x = v[u * GL + q];
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < Cfg::LIN; i++) {
+            const int e = tid + i * Cfg::THREADS;
+            if ((Cfg::P * N) % Cfg::THREADS == 0 || e < Cfg::P * N) {
+                const LdsT &x = lds[(e / N) * Cfg::LS + lds_pos(e % N)];
+                if constexpr (!Cfg::SPLIT) lin[i] = x;
+                else if constexpr (part) lin[i].y = x;
+                else lin[i].x = x;
+            }
+        }
+    });
+}
+
 #ifdef FB_WAVES_PER_EU
 #define FB_OCCUPANCY __attribute__((amdgpu_waves_per_eu(FB_WAVES_PER_EU)))
 #else
@@ -435,8 +530,9 @@ __device__ __forceinline__ void store_tile_contiguous(const PassArgs &a, int64_t
 // One tile of a pass: P pencils of length N.  `lds` holds P * LS elements,
 // `gtab` N reals (contiguous passes).  The caller may run the tile on a
 // workgroup larger than the tile's THREADS (the persistent batch kernel):
-// the extra threads only take part in the barriers.
-template <typename V, int N, bool CONTIG, bool MX, bool MULTI = false, bool NT = false>
+// the extra threads only take part in the barriers.  STAGE_OK: the workgroup
+// is the tile's THREADS, so that tiles may move as one block (PassCfg::block).
+template <typename V, int N, bool CONTIG, bool MX, bool MULTI = false, bool NT = false, bool STAGE_OK = false>
 __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int tid, V *lds, real_t<V> *gtab)
 {
     using Cfg = PassCfg<V, N, CONTIG, MX>;
@@ -522,7 +618,24 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
             }
         }
     };
-    if (valid && !MX_IN) {
+    // the tile is one block of memory (uniform): pencils back to back
+    constexpr bool STAGE = STAGE_OK && Cfg::block(NT && nt_load<V, CONTIG>());
+    [[maybe_unused]] const bool block = STAGE && !a.seg_off && !ogeom && a.inner == 1 && a.outer == N && S == 1;
+    [[maybe_unused]] const int64_t block0 = tile * P * N;   // its first element, and its length
+    [[maybe_unused]] const int block_n = (int)(a.npencils - tile * P < P ? a.npencils - tile * P : P) * N;
+    using LdsT = typename Cfg::LdsT;
+    if (STAGE && block && !a.gen) {
+        if constexpr (STAGE) {
+            V lin[Cfg::LIN];
+            const V *src = (const V *)a.in + block0;
+#pragma unroll
+            for (int i = 0; i < Cfg::LIN; i++) {   // past the end: the last element again
+                const int e = tid + i * Cfg::THREADS;
+                lin[i] = ld_stream<NT && nt_load<V, CONTIG>()>(src + (e < block_n ? e : block_n - 1));
+            }
+            block_to_rows<Cfg, N>(lin, v, tid, t, (LdsT *)lds, (LdsT *)lds + pp * LS);
+        }
+    } else if (valid && !MX_IN) {
         if (a.gen) {
 #pragma unroll
             for (int u = 0; u < U0; u++) {
@@ -836,6 +949,25 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                 }
             }
         };
+        if constexpr (STAGE) {
+            if (block) {   // uniform
+                const R sc = (R)a.scale;
+#pragma unroll
+                for (int i = 0; i < M; i++) {
+                    if (a.inv) v[i] = cconj(v[i]);
+                    if (a.scale != 1.0) v[i] = cscale(v[i], sc);
+                }
+                V lin[Cfg::LIN];
+                rows_to_block<Cfg, N>(v, lin, tid, t, (LdsT *)lds, (LdsT *)lds + pp * LS);
+                V *dst = (V *)a.out + block0 + (MULTI ? rep * a.out_step : 0);
+#pragma unroll
+                for (int i = 0; i < Cfg::LIN; i++) {
+                    const int e = tid + i * Cfg::THREADS;
+                    if (e < block_n) st_stream<NT && nt_store<V, CONTIG>()>(dst + e, lin[i]);
+                }
+                return;
+            }
+        }
         if (valid && !MX_OUT) {
             store_all(std::integral_constant<bool, NT && nt_store<V, CONTIG>()>{});
         }
@@ -897,7 +1029,7 @@ __global__ void __launch_bounds__((PassCfg<V, N, CONTIG, MX>::THREADS)) FB_OCCUP
     using Cfg = PassCfg<V, N, CONTIG, MX>;
     __shared__ typename Cfg::LdsT lds[Cfg::P * Cfg::LS];
     __shared__ real_t<V> gtab[CONTIG ? N : 1];
-    pass_tile<V, N, CONTIG, MX, false, NT>(a, tile_of_block<xcd_remap<V, N, CONTIG, MX>()>(blockIdx.x, gridDim.x),
+    pass_tile<V, N, CONTIG, MX, false, NT, true>(a, tile_of_block<xcd_remap<V, N, CONTIG, MX>()>(blockIdx.x, gridDim.x),
                                            threadIdx.x, (V *)lds, gtab);
 }
 
@@ -910,7 +1042,7 @@ __global__ void __launch_bounds__((PassCfg<V, N, true, MX>::THREADS)) FB_OCCUPAN
     using Cfg = PassCfg<V, N, true, MX>;
     __shared__ typename Cfg::LdsT lds[Cfg::P * Cfg::LS];
     __shared__ real_t<V> gtab[N];
-    pass_tile<V, N, true, MX, true, NT>(a, tile_of_block<xcd_remap<V, N, true, MX>()>(blockIdx.x, gridDim.x),
+    pass_tile<V, N, true, MX, true, NT, true>(a, tile_of_block<xcd_remap<V, N, true, MX>()>(blockIdx.x, gridDim.x),
                                         threadIdx.x, (V *)lds, gtab);
 }
 

@@ -68,11 +68,11 @@ constexpr bool supported_length_b1(int64_t n)
 constexpr int threads_per_pencil(int n) { return (n % 16 == 0) ? n / 16 : n <= 32 ? 1 : (n + 15) / 16; }
 
 // Whether a pass works its stages in groups (group_plan): the lengths whose
-// radix list repeats the radix 3, on the vector units.  Short contiguous
-// passes would leave a pencil one or two threads, whose loads then lie a
-// pencil apart (27 points: 37 us stage by stage on two threads, 59 us as one
-// group on one thread); they keep single stages.
-constexpr bool grouped(int n, bool contig, bool mx) { return n % 9 == 0 && !mx && (!contig || n >= 81); }
+// radix list repeats the radix 3, on the vector units.  54 and 72 points stay
+// stage by stage in contiguous passes: as groups they take 3 threads instead
+// of 4 and 5, whose loads lie further apart (72: 16.8 -> 19.0 us); the shorter
+// ones move their tiles as one block, where that does not matter.
+constexpr bool grouped(int n, bool contig, bool mx) { return n % 9 == 0 && !mx && (!contig || n <= 48 || n >= 81); }
 
 // Stages worked together in registers.  A group of consecutive stages of
 // radices R_s .. R_e and product G is a set of N/G independent butterflies of

@@ -133,6 +133,30 @@ def test_grouped_stages_part_filled_tiles(shape, dtype):
         assert torch.equal(one, multi[j]), j
 
 
+@pytest.mark.parametrize("shape,dtype", [((1, 1, 8), fb.FB_C64), ((3, 243, 16), fb.FB_C64), ((1, 81, 27), fb.FB_C128),
+                                         ((9, 9, 48), fb.FB_C128), ((2, 27, 36), fb.FB_C64_SPLITBF16),
+                                         # above 192 MiB: non-temporal accesses
+                                         ((243, 243, 216), fb.FB_C128), ((486, 324, 162), fb.FB_C64)])
+def test_tiles_moved_as_one_block(shape, dtype):
+    """Contiguous passes whose tiles are loaded and stored as one block of
+    memory, with a part-filled last tile: a single axis, out of place and in
+    place, both directions; nothing past the grid is written."""
+    print(f"block tiles shape={shape} dtype={dtype}", flush=True)
+    n = math.prod(shape)
+    x = as_seen(inputs.uniform_grid(shape, 13), dtype)
+    plan = fb.Plan(*shape, dtype)
+    t = dev(x, dtype)
+    buf = torch.full((n + 64,), 7.0, dtype=plan.torch_dtype, device="cuda")
+    out = buf[:n].view(shape)
+    for direction in (fb.FB_FORWARD, fb.FB_INVERSE):
+        fb.fb_fft3d_exec_axes(plan, t, out, direction, 1)
+        ref = oracle.fft1d_many(x.reshape(-1, shape[2]), direction).reshape(shape)
+        assert rel_l2(host(out), ref) < TOL[dtype], direction
+        assert torch.all(buf[n:] == 7.0)
+    fb.fb_fft3d_exec_axes(plan, t, t, fb.FB_INVERSE, 1)
+    assert torch.equal(t, out)
+
+
 def test_round_trip_c128():
     shape = (64, 32, 96)
     x = inputs.uniform_grid(shape, 5)
