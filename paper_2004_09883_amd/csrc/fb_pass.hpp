@@ -40,15 +40,21 @@ namespace fb {
 
 __device__ __forceinline__ int64_t signed_k(int64_t i, int64_t n) { return (2 * i >= n) ? i - n : i; }
 
-template <typename V, int N, bool CONTIG, bool MX = false> struct PassCfg {
+template <typename V, int N, bool CONTIG, bool MX = false, bool NT = false> struct PassCfg {
     // complex128 tiles exchange real and imaginary parts in two rounds
-    static constexpr bool SPLIT = FB_SPLIT_EXCHANGE && std::is_same<V, double2>::value && N <= FB_SPLIT_MAX_N;
+    static constexpr bool SPLIT = std::is_same<V, double2>::value && split_exchange(N, CONTIG, NT);
     using LdsT = typename std::conditional<SPLIT, double, V>::type;   // LDS element
     static constexpr RadixPlan RP = radix_plan(N);
     static constexpr GroupPlan GP = group_plan(N, grouped(N, CONTIG, MX));
     static constexpr int T = GP.threads;
     static constexpr int P = pencils_per_wg(N, CONTIG, (int)sizeof(V), MX, SPLIT);
     static constexpr int THREADS = P * T;
+    // waves per SIMD the kernel's registers must leave room for (1: no
+    // demand): two 512-thread tiles per CU for the wide strided passes (1024
+    // points 299 -> 270 us, 576: 167 -> 146); not where part-filled rounds of
+    // radix-3 butterflies would spill (768 points 210 -> 242)
+    static constexpr int MIN_WAVES =
+        SPLIT && wide_strided(N, CONTIG, NT) && (GP.elems <= 16 || (N % 9 == 0 && GP.elems <= 18)) ? 4 : 1;
     static constexpr int M = GP.elems;
     static constexpr int LS = lds_pencil_stride(N);
     // whether a contiguous tile moves as one block (block_to_rows), with
@@ -535,7 +541,7 @@ __device__ __forceinline__ void rows_to_block(const V (&v)[M], V (&lin)[Cfg::LIN
 template <typename V, int N, bool CONTIG, bool MX, bool MULTI = false, bool NT = false, bool STAGE_OK = false>
 __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int tid, V *lds, real_t<V> *gtab)
 {
-    using Cfg = PassCfg<V, N, CONTIG, MX>;
+    using Cfg = PassCfg<V, N, CONTIG, MX, NT>;
     using R = real_t<V>;
     constexpr RadixPlan RP = Cfg::RP;
     constexpr GroupPlan GP = Cfg::GP;
@@ -1013,9 +1019,9 @@ template <bool REMAP> __device__ __forceinline__ int64_t tile_of_block(int64_t b
 #ifndef FB_XCD_REMAP_NARROW
 #define FB_XCD_REMAP_NARROW 1
 #endif
-template <typename V, int N, bool CONTIG, bool MX> constexpr bool xcd_remap()
+template <typename V, int N, bool CONTIG, bool MX, bool NT> constexpr bool xcd_remap()
 {
-    constexpr int seg_bytes = PassCfg<V, N, CONTIG, MX>::P * (int)sizeof(V);
+    constexpr int seg_bytes = PassCfg<V, N, CONTIG, MX, NT>::P * (int)sizeof(V);
     return FB_XCD_REMAP || (FB_XCD_REMAP_MX_STRIDED && MX && !CONTIG) ||
            (FB_XCD_REMAP_NARROW && !CONTIG && seg_bytes < 128);
 }
@@ -1024,12 +1030,13 @@ template <typename V, int N, bool CONTIG, bool MX> constexpr bool xcd_remap()
 template <typename V, bool CONTIG> constexpr bool has_nt() { return nt_load<V, CONTIG>() || nt_store<V, CONTIG>(); }
 
 template <typename V, int N, bool CONTIG, bool MX, bool NT = false>
-__global__ void __launch_bounds__((PassCfg<V, N, CONTIG, MX>::THREADS)) FB_OCCUPANCY fft_pass(PassArgs a)
+__global__ void __launch_bounds__((PassCfg<V, N, CONTIG, MX, NT>::THREADS), (PassCfg<V, N, CONTIG, MX, NT>::MIN_WAVES))
+    FB_OCCUPANCY fft_pass(PassArgs a)
 {
-    using Cfg = PassCfg<V, N, CONTIG, MX>;
+    using Cfg = PassCfg<V, N, CONTIG, MX, NT>;
     __shared__ typename Cfg::LdsT lds[Cfg::P * Cfg::LS];
     __shared__ real_t<V> gtab[CONTIG ? N : 1];
-    pass_tile<V, N, CONTIG, MX, false, NT, true>(a, tile_of_block<xcd_remap<V, N, CONTIG, MX>()>(blockIdx.x, gridDim.x),
+    pass_tile<V, N, CONTIG, MX, false, NT, true>(a, tile_of_block<xcd_remap<V, N, CONTIG, MX, NT>()>(blockIdx.x, gridDim.x),
                                            threadIdx.x, (V *)lds, gtab);
 }
 
@@ -1037,12 +1044,12 @@ __global__ void __launch_bounds__((PassCfg<V, N, CONTIG, MX>::THREADS)) FB_OCCUP
 // once and output j (evolution constant ev_cs[j]) is written at
 // out + j out_step, for j < nout.
 template <typename V, int N, bool MX, bool NT = false>
-__global__ void __launch_bounds__((PassCfg<V, N, true, MX>::THREADS)) FB_OCCUPANCY fft_pass_multi(PassArgs a)
+__global__ void __launch_bounds__((PassCfg<V, N, true, MX, NT>::THREADS)) FB_OCCUPANCY fft_pass_multi(PassArgs a)
 {
-    using Cfg = PassCfg<V, N, true, MX>;
+    using Cfg = PassCfg<V, N, true, MX, NT>;
     __shared__ typename Cfg::LdsT lds[Cfg::P * Cfg::LS];
     __shared__ real_t<V> gtab[N];
-    pass_tile<V, N, true, MX, true, NT, true>(a, tile_of_block<xcd_remap<V, N, true, MX>()>(blockIdx.x, gridDim.x),
+    pass_tile<V, N, true, MX, true, NT, true>(a, tile_of_block<xcd_remap<V, N, true, MX, NT>()>(blockIdx.x, gridDim.x),
                                         threadIdx.x, (V *)lds, gtab);
 }
 

@@ -11,7 +11,7 @@ namespace fb {
 template <typename V, int N, bool CONTIG, bool MX, bool NT = false>
 hipError_t launch_pass(const PassArgs &a, hipStream_t st)
 {
-    using Cfg = PassCfg<V, N, CONTIG, MX>;
+    using Cfg = PassCfg<V, N, CONTIG, MX, NT>;
     constexpr int64_t UNIT = std::is_same<V, c2x>::value ? 2 : 1;   // pencils per tile slot
     const int64_t blocks = (a.npencils + UNIT * Cfg::P - 1) / (UNIT * Cfg::P);
     if (blocks <= 0) return hipSuccess;
@@ -92,7 +92,7 @@ template <bool B3> PassInfo find_pass_pair_t(int n, bool mx)
 
 template <typename V, int N, bool MX, bool NT = false> hipError_t launch_pass_multi(const PassArgs &a, hipStream_t st)
 {
-    using Cfg = PassCfg<V, N, true, MX>;
+    using Cfg = PassCfg<V, N, true, MX, NT>;
     const int64_t blocks = (a.npencils + Cfg::P - 1) / Cfg::P;
     if (blocks <= 0) return hipSuccess;
     hipLaunchKernelGGL((fft_pass_multi<V, N, MX, NT>), dim3((unsigned)blocks), dim3(Cfg::THREADS), 0, st, a);

@@ -288,8 +288,43 @@ constexpr int grouped_pencils(int n, int threads, bool contig, int esize, bool s
     return 1;
 }
 
+// Pencils per workgroup of the long strided complex128 passes (wide_strided
+// below): 8, a whole 128-byte line per row, while the workgroup's LDS (one
+// real part per element) and threads allow it, then 4.  More than 512 threads
+// leave 128 registers each, enough for 18 elements per thread.
+constexpr int wide_pencils(int n, int threads, int elems)
+{
+    int p = 8;
+    while (p > 1 && (p * threads > (elems <= 18 ? 1024 : 512) || p * lds_pencil_stride(n) * 8 > 150 * 1024)) p /= 2;
+    return p;
+}
+
+// Long strided complex128 passes with tiles of whole 128-byte lines per row
+// (wide_pencils).  With the 72 KB of one-round tiles a row segment is 64 bytes
+// at 1024 points and 16 at 4096, and the lines that neighbouring tiles share
+// have left the L2 before their turn.  A two-round exchange halves the tile's
+// LDS, and one tile may take most of a CU's.  Measured on grids above 192 MiB
+// (narrow -> wide, us): 576 points 180 -> 146, 768: 262 -> 210, 1024: 361 ->
+// 270, 1458: 478 -> 194, 2048: 723 -> 306, 4096: 1300 -> 455.  Grids that the
+// last-level cache holds gain past 2048 points only (64 MiB: 2304 28.2 -> 22.5,
+// 4096 43.8 -> 40.6, but 1024 26.1 -> 39.4 and 768 22.6 -> 26.1), so shorter
+// passes are wide in their non-temporal instance (nt) alone.
+constexpr bool wide_strided(int n, bool contig, bool nt) { return FB_SPLIT_EXCHANGE && !contig && n > (nt ? 512 : 2048); }
+// Whether a complex128 pass exchanges real and imaginary parts in two rounds:
+// up to 256 points it lets more tiles share a CU (at 257 .. 512 points one
+// round was faster, the 512-point x pass 196 against 215 us), and the wide
+// strided passes need it.
+constexpr bool split_exchange(int n, bool contig, bool nt)
+{
+    return (FB_SPLIT_EXCHANGE && n <= FB_SPLIT_MAX_N) || wide_strided(n, contig, nt);
+}
+
 constexpr int pencils_per_wg(int n, bool contig, int esize, bool mx = false, bool split = false)
 {
+    if (split && !contig && n > 512) {
+        const GroupPlan gp = group_plan(n, grouped(n, contig, mx));
+        return wide_pencils(n, gp.threads, gp.elems);
+    }
     if (grouped(n, contig, mx)) return grouped_pencils(n, group_plan(n, true).threads, contig, esize, split);
     if (mx) {
         const int P = pencils_per_wg_b(n, contig, esize, true, split);

@@ -157,6 +157,24 @@ def test_tiles_moved_as_one_block(shape, dtype):
     assert torch.equal(t, out)
 
 
+@pytest.mark.parametrize("shape", [(576, 243, 96), (1024, 9, 1458), (2048, 81, 81), (4096, 1, 3456),
+                                   (1, 2187, 36), (3, 2304, 27), (1, 3888, 9)])
+def test_wide_strided_tiles_c128(shape):
+    """Long strided complex128 passes with whole lines per row, on grids above
+    the last-level cache (and past 2048 points on small ones), with pencil
+    counts that are no multiple of the tile: against the oracle, in place."""
+    axis = 2 if shape[0] > 512 else 1
+    print(f"wide strided shape={shape}", flush=True)
+    x = inputs.uniform_grid(shape, 17)
+    plan = fb.Plan(*shape, fb.FB_C128)
+    rows = np.ascontiguousarray(np.moveaxis(x, 2 - axis, 2))
+    for direction in (fb.FB_FORWARD, fb.FB_INVERSE):
+        t = dev(x, fb.FB_C128)
+        fb.fb_fft3d_exec_axes(plan, t, t, direction, 1 << axis)
+        ref = oracle.fft1d_many(rows.reshape(-1, shape[2 - axis]), direction).reshape(rows.shape)
+        assert rel_l2(np.moveaxis(host(t), 2 - axis, 2), ref) < TOL[fb.FB_C128], direction
+
+
 def test_round_trip_c128():
     shape = (64, 32, 96)
     x = inputs.uniform_grid(shape, 5)
