@@ -967,6 +967,7 @@ bool build_onelaunch_items(const std::vector<fb::BatchGroup> &groups, const std:
 bool group_in_bounds(const fb::BatchGroup &g, int64_t seg_max_off, int64_t total)
 {
     const PassArgs &a = g.args;
+    if (!fb::pass_args_ok(a, g.contig != 0)) return false;
     const int64_t np = a.seg_pencils;
     auto reach = [&](int64_t inner, int64_t outer, int64_t istep, int64_t stride) {
         const int64_t in_max = (np < inner ? np : inner) - 1;

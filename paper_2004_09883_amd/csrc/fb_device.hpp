@@ -28,9 +28,14 @@ template <typename V> using tw_t = typename vec_traits<V>::tw;
 template <typename V> __device__ __forceinline__ V mk(real_t<V> x, real_t<V> y) { V r; r.x = x; r.y = y; return r; }
 template <typename V> __device__ __forceinline__ V cadd(V a, V b) { return mk<V>(a.x + b.x, a.y + b.y); }
 template <typename V> __device__ __forceinline__ V csub(V a, V b) { return mk<V>(a.x - b.x, a.y - b.y); }
+// The products are fused by hand: left to the compiler, which of the two
+// products of a sum is the rounded one depends on the code around it, and the
+// same pass compiled into two kernels would not give the same bits.
+__device__ __forceinline__ double fused(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ float fused(float a, float b, float c) { return fmaf(a, b, c); }
 template <typename V> __device__ __forceinline__ V cmul(V a, V b)
 {
-    return mk<V>(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return mk<V>(fused(a.x, b.x, -(a.y * b.y)), fused(a.y, b.x, a.x * b.y));
 }
 template <typename V> __device__ __forceinline__ V cconj(V a) { return mk<V>(a.x, -a.y); }
 template <typename V> __device__ __forceinline__ V cscale(V a, real_t<V> s) { return mk<V>(a.x * s, a.y * s); }
@@ -43,12 +48,18 @@ __device__ __forceinline__ c2x cadd(c2x p, c2x q) { return mk2(mkf(p.a.x + q.a.x
 __device__ __forceinline__ c2x csub(c2x p, c2x q) { return mk2(mkf(p.a.x - q.a.x, p.a.y - q.a.y), mkf(p.b.x - q.b.x, p.b.y - q.b.y)); }
 __device__ __forceinline__ c2x cmul(c2x p, float2 w)
 {
-    return mk2(mkf(p.a.x * w.x - p.a.y * w.y, p.a.x * w.y + p.a.y * w.x),
-               mkf(p.b.x * w.x - p.b.y * w.y, p.b.x * w.y + p.b.y * w.x));
+    return mk2(cmul(p.a, w), cmul(p.b, w));
 }
 __device__ __forceinline__ c2x cconj(c2x p) { return mk2(mkf(p.a.x, -p.a.y), mkf(p.b.x, -p.b.y)); }
 __device__ __forceinline__ c2x cscale(c2x p, float s) { return mk2(mkf(p.a.x * s, p.a.y * s), mkf(p.b.x * s, p.b.y * s)); }
 __device__ __forceinline__ c2x mul_mi(c2x p) { return mk2(mkf(p.a.y, -p.a.x), mkf(p.b.y, -p.b.x)); }
+
+// a s + c
+template <typename V> __device__ __forceinline__ V cfma(V a, real_t<V> s, V c)
+{
+    return mk<V>(fused(a.x, s, c.x), fused(a.y, s, c.y));
+}
+__device__ __forceinline__ c2x cfma(c2x p, float s, c2x c) { return mk2(cfma(p.a, s, c.a), cfma(p.b, s, c.b)); }
 
 // Exact-value constants of the small roots of unity (math constants, written
 // to more digits than binary64 holds; the compiler rounds them).
@@ -59,14 +70,20 @@ struct K {
     static constexpr double S3 = 0.86602540378443864676372317075293618347;  // sqrt(3)/2
 };
 
-// a * w where w = (c, s) given as constants
-template <typename V> __device__ __forceinline__ V cmulc(V a, double c, double s)
+// a * w where w = (c, s) given as constants.  XFIRST: the products with a.x are
+// the ones that are not rounded; as it stands in each place below, it keeps
+// the library's results what they were when the compiler chose.
+template <bool XFIRST = false, typename V> __device__ __forceinline__ V cmulc(V a, double c, double s)
 {
     using R = real_t<V>;
     const R cr = (R)c, ci = (R)s;
-    return mk<V>(a.x * cr - a.y * ci, a.x * ci + a.y * cr);
+    if constexpr (XFIRST) return mk<V>(fused(a.x, cr, -(a.y * ci)), fused(a.x, ci, a.y * cr));
+    return mk<V>(fused(a.y, -ci, a.x * cr), fused(a.y, cr, a.x * ci));
 }
-__device__ __forceinline__ c2x cmulc(c2x p, double c, double s) { return cmul(p, make_float2((float)c, (float)s)); }
+template <bool XFIRST = false> __device__ __forceinline__ c2x cmulc(c2x p, double c, double s)
+{
+    return mk2(cmulc<XFIRST>(p.a, c, s), cmulc<XFIRST>(p.b, c, s));
+}
 
 template <typename V> __device__ __forceinline__ void dft2(V &a0, V &a1)
 {
@@ -82,11 +99,10 @@ template <typename V> __device__ __forceinline__ void dft3(V &a0, V &a1, V &a2)
     const V s = cadd(a1, a2);
     const V d = csub(a1, a2);
     const V m = csub(a0, cscale(s, (R)0.5));
-    // -i * S3 * d
-    const V r = cscale(mul_mi(d), (R)K::S3);
+    const V e = mul_mi(d);   // r = S3 e
     a0 = cadd(a0, s);
-    a1 = cadd(m, r);
-    a2 = csub(m, r);
+    a1 = cfma(e, (R)K::S3, m);
+    a2 = cfma(e, -(R)K::S3, m);
 }
 
 template <typename V> __device__ __forceinline__ void dft4(V &a0, V &a1, V &a2, V &a3)
@@ -116,8 +132,8 @@ template <typename V> __device__ __forceinline__ void dft8(V *a)
 }
 
 // 16 = 4 x 4: index n = 4 n1 + n2, output k = k1 + 4 k2;
-// inner twiddle w16^(n2 k1)
-template <typename V> __device__ __forceinline__ void dft16(V *a)
+// inner twiddle w16^(n2 k1).  TW: the inputs were multiplied by twiddles.
+template <bool TW, typename V> __device__ __forceinline__ void dft16(V *a)
 {
     V y[4][4];
 #pragma unroll
@@ -134,8 +150,8 @@ template <typename V> __device__ __forceinline__ void dft16(V *a)
     y[2][2] = mul_mi(y[2][2]);                 // m = 4
     y[2][3] = cmulc(y[2][3], -K::R2, -K::R2);  // m = 6
     y[3][1] = cmulc(y[3][1], K::S8, -K::C8);   // m = 3
-    y[3][2] = cmulc(y[3][2], -K::R2, -K::R2);  // m = 6
-    y[3][3] = cmulc(y[3][3], -K::C8, K::S8);   // m = 9
+    y[3][2] = cmulc<TW>(y[3][2], -K::R2, -K::R2);  // m = 6
+    y[3][3] = cmulc<true>(y[3][3], -K::C8, K::S8);   // m = 9
 #pragma unroll
     for (int k1 = 0; k1 < 4; k1++) {
         V b0 = y[0][k1], b1 = y[1][k1], b2 = y[2][k1], b3 = y[3][k1];
@@ -144,18 +160,26 @@ template <typename V> __device__ __forceinline__ void dft16(V *a)
     }
 }
 
-template <int R, typename V> __device__ __forceinline__ void dft(V *a)
+template <int R, bool TW, typename V> __device__ __forceinline__ void dft(V *a)
 {
     if constexpr (R == 2) dft2(a[0], a[1]);
     else if constexpr (R == 3) dft3(a[0], a[1], a[2]);
     else if constexpr (R == 4) dft4(a[0], a[1], a[2], a[3]);
     else if constexpr (R == 8) dft8(a);
-    else if constexpr (R == 16) dft16(a);
+    else if constexpr (R == 16) dft16<TW>(a);
     else static_assert(R == 2, "unsupported radix");
 }
 
 // Padded LDS position of element i of a pencil row: one pad slot every 16.
 __device__ __forceinline__ int lds_pos(int i) { return i + (i >> 4); }
+// lds_pos(i + C) for a constant C: whole groups of 16 are a constant distance
+// (an immediate offset of the access) from lds_pos(i).  GROUP_START: i is a
+// multiple of 16, so any C is.
+template <int C, bool GROUP_START = false> __device__ __forceinline__ int lds_pos_plus(int i)
+{
+    if constexpr (C % 16 == 0 || GROUP_START) return lds_pos(i) + C + C / 16;
+    else return lds_pos(i + C);
+}
 
 // exp(-c k2): binary64 for complex128 grids, binary32 for complex64 grids.
 template <typename R> __device__ __forceinline__ R evol_factor(double c, double k2)

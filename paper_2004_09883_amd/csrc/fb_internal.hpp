@@ -65,6 +65,17 @@ struct PassArgs {
     double ev_cs[FB_MAX_FUSED_STEPS];
 };
 
+// What the kernels' index arithmetic takes for granted: pencil numbers, a
+// tile's overhang included, fit 32 bits, and a contiguous pass has stride 1,
+// pencils `outer` apart and no output geometry of its own.
+inline bool pass_args_ok(const PassArgs &a, bool contig)
+{
+    if (a.npencils >= (int64_t(1) << 32) - (1 << 16) || a.inner < 1 || a.inner >= int64_t(1) << 32) return false;
+    if (a.ostride && (a.oinner < 1 || a.oinner >= int64_t(1) << 32)) return false;
+    if (a.evolve && (a.ev_d < 1 || a.ev_d >= int64_t(1) << 32)) return false;
+    return !contig || (a.inner == 1 && a.stride == 1 && a.ostride == 0);
+}
+
 // Data swept by one pass above which its global accesses may be
 // non-temporal (the MI355X last-level cache is 256 MB; grids of 128 MiB and
 // less gain from it between passes).

@@ -25,8 +25,16 @@
 // complex outputs k = 4g..4g+3.
 #pragma once
 #include "fb_device.hpp"
+#include "fb_plan_rules.hpp"
 
 namespace fb {
+
+// a * b ahead of the split into bf16 parts, fused as the compiler chooses
+__device__ __forceinline__ float2 mx_cmul(float2 a, float2 b)
+{
+    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -121,7 +129,12 @@ __device__ __forceinline__ void mx_stage16(const float2 *__restrict__ tw, const 
             const int q = 4 * g + i;
             float2 v = src.load(h, b + q * NBF);
             if constexpr (Ns > 1) {
-                if (q > 0) v = cmul(v, tw[TWOFF + (q - 1) * Ns + (b % Ns)]);
+                // (each form where it keeps the results that the stage always had)
+                if (q > 0) {
+                    const float2 w = tw[TWOFF + (q - 1) * Ns + (b % Ns)];
+                    constexpr RadixPlan RP = radix_plan(N);
+                    v = G == 4 && RP.r[RP.count - 1] != 2 ? cmul(v, w) : mx_cmul(v, w);
+                }
             }
             x[gi][i] = v;
         }
@@ -246,7 +259,7 @@ __device__ __forceinline__ void mx_stage16_reg(const float2 *__restrict__ tw, co
                 if (q > 0) {
                     const float2 w = tw[TWOFF + (q - 1) * Ns + (b % Ns)];
 #pragma unroll
-                    for (int h = 0; h < SETS; h++) x[h][gm][i] = cmul(x[h][gm][i], w);
+                    for (int h = 0; h < SETS; h++) x[h][gm][i] = mx_cmul(x[h][gm][i], w);
                 }
             }
         }

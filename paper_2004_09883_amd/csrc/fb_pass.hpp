@@ -38,7 +38,38 @@
 
 namespace fb {
 
-__device__ __forceinline__ int64_t signed_k(int64_t i, int64_t n) { return (2 * i >= n) ? i - n : i; }
+__device__ __forceinline__ int signed_k(int i, int n) { return (2 * i >= n) ? i - n : i; }
+
+// Index arithmetic of a pass.  A tile's elements lie at (thread part) +
+// (uniform part): the thread's pencil and first row, and a multiple of the
+// stride that is the same for every thread.  Kept apart, the second is scalar
+// work and an access costs one 64-bit vector addition; pencil numbers are
+// 32-bit (checked at the launch), since a 64-bit division takes about a
+// hundred instructions.  A contiguous pass has stride 1 and pencils `outer`
+// apart.  The executed instructions of the 256-point strided complex128 pass
+// fall by a third; the passes that HBM bounds stay where they were, the others
+// gain: 512-point contiguous 22.4 -> 21.4 us on 64 MiB, the 8-output 128-point
+// evolve pass 29 -> 22 us, 512x256x256 split-bf16 round trip 611 -> 590 us.
+struct PencilAt {
+    uint32_t seg, local;   // segment and pencil within it
+};
+__device__ __forceinline__ PencilAt pencil_at(const PassArgs &a, uint32_t p)
+{
+    if (!a.seg_off) return {0u, p};
+    const uint32_t sp = (uint32_t)a.seg_pencils, s = p / sp;
+    return {s, p - s * sp};
+}
+template <bool CONTIG> __device__ __forceinline__ int64_t pencil_base(const PassArgs &a, uint32_t local)
+{
+    if constexpr (CONTIG) return (int64_t)local * a.outer;
+    const uint32_t in = (uint32_t)a.inner, q = local / in;
+    return (int64_t)q * a.outer + (int64_t)(local - q * in) * a.istep;
+}
+__device__ __forceinline__ int64_t pencil_obase(const PassArgs &a, uint32_t local)
+{
+    const uint32_t in = (uint32_t)a.oinner, q = local / in;
+    return (int64_t)q * a.oouter + (int64_t)(local - q * in) * a.oistep;
+}
 
 template <typename V, int N, bool CONTIG, bool MX = false, bool NT = false> struct PassCfg {
     // complex128 tiles exchange real and imaginary parts in two rounds
@@ -64,6 +95,16 @@ template <typename V, int N, bool CONTIG, bool MX = false, bool NT = false> stru
         constexpr int seg = T * (int)sizeof(V);   // bytes of a pencil that its threads access together
         if (!CONTIG || MX) return false;
         return nt ? N < 512 && seg % 128 != 0 && (seg < 128 || N % 9 == 0 || !SPLIT) : N <= 48;
+    }
+    // LDS elements of a pass kernel's tile.  Non-temporal contiguous tiles of
+    // up to 256 complex128 points ask for 20 KB per wavefront, which keeps 8 of
+    // them on a CU: with the 14 that their registers and rows allow, the grid
+    // streams in from too many places at once (256 points 171 -> 165 us at 512
+    // MiB, 128: 175 -> 169)
+    static constexpr int lds_elems(bool nt)
+    {
+        const int floor = nt && CONTIG && SPLIT && !block(nt) ? (20 * 1024 * THREADS / 64 - N * 8) / 8 : 0;
+        return P * LS > floor ? P * LS : floor;
     }
     static constexpr int LIN = (N + T - 1) / T;   // elements per thread of a tile moved as one block
     static_assert(RP.count >= 1, "pass needs at least one stage");
@@ -370,7 +411,7 @@ template <typename Cfg, int S, typename V> __device__ __forceinline__ void group
 #pragma unroll
                     for (int q = 1; q < R; q++) a[q] = cmul(a[q], tw[RP.twoff[s] + (q - 1) * Ns + k + kq]);
                 }
-                dft<R>(a);
+                dft<R, (Ns > 1)>(a);
 #pragma unroll
                 for (int q = 0; q < R; q++) w[Q * R * GN + q * GN + j] = a[q];
             }
@@ -413,17 +454,13 @@ __device__ __forceinline__ void store_tile_contiguous(const PassArgs &a, int64_t
         }
     }
     __syncthreads();
-    const int64_t p0 = tile * P * UNIT;   // first pencil of the tile
-    if (active && p0 < a.npencils) {
-        int64_t seg0 = 0, lp0 = p0;
-        if (a.seg_off) {
-            seg0 = a.seg_off[p0 / a.seg_pencils];
-            lp0 = p0 % a.seg_pencils;
-        }
-        const int64_t ob = seg0 + (a.ostride ? (lp0 / a.oinner) * a.oouter + (lp0 % a.oinner) * a.oistep
-                                             : (lp0 / a.inner) * a.outer + (lp0 % a.inner) * a.istep);
-        const int64_t np = a.npencils - p0 < P * UNIT ? a.npencils - p0 : P * UNIT;
-        const int count = (int)np * N;
+    const uint32_t p0 = (uint32_t)tile * (P * UNIT);   // first pencil of the tile
+    if (active && p0 < (uint32_t)a.npencils) {
+        const PencilAt w = pencil_at(a, p0);
+        const int64_t ob = (a.seg_off ? a.seg_off[w.seg] : 0) +
+                           (a.ostride ? pencil_obase(a, w.local) : pencil_base<CONTIG>(a, w.local));
+        const uint32_t left = (uint32_t)a.npencils - p0;
+        const int count = (int)(left < P * UNIT ? left : P * UNIT) * N;
         elem_t<V> *o = (elem_t<V> *)a.out + ob;
         auto store_all = [&](auto ntc) {
             constexpr bool NTA = decltype(ntc)::value;
@@ -536,9 +573,10 @@ __device__ __forceinline__ void rows_to_block(const V (&v)[M], V (&lin)[Cfg::LIN
 // One tile of a pass: P pencils of length N.  `lds` holds P * LS elements,
 // `gtab` N reals (contiguous passes).  The caller may run the tile on a
 // workgroup larger than the tile's THREADS (the persistent batch kernel):
-// the extra threads only take part in the barriers.  STAGE_OK: the workgroup
-// is the tile's THREADS, so that tiles may move as one block (PassCfg::block).
-template <typename V, int N, bool CONTIG, bool MX, bool MULTI = false, bool NT = false, bool STAGE_OK = false>
+// the extra threads only take part in the barriers.  OWN: the tile of a pass
+// kernel of its own, whose workgroup is the tile's THREADS; only there may it
+// move as one block (PassCfg::block), generate its input or evolve it.
+template <typename V, int N, bool CONTIG, bool MX, bool MULTI = false, bool NT = false, bool OWN = false>
 __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int tid, V *lds, real_t<V> *gtab)
 {
     using Cfg = PassCfg<V, N, CONTIG, MX, NT>;
@@ -558,21 +596,19 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
     const bool active = tid < Cfg::THREADS;
     const int t = CONTIG ? tid % T : tid / P;
     const int pp = CONTIG ? tid / T : tid % P;
-    const int64_t p = (tile * P + pp) * (PAIR ? 2 : 1);   // (first) pencil of this thread
-    const bool valid = active && p < a.npencils;
-    int64_t seg0 = 0, lp = p;   // segment start and local pencil index
-    if (a.seg_off && valid) {
-        seg0 = a.seg_off[p / a.seg_pencils];
-        lp = p % a.seg_pencils;
-    }
-    const int64_t base = valid ? seg0 + (lp / a.inner) * a.outer + (lp % a.inner) * a.istep : 0;
-    const bool ogeom = a.ostride != 0;
-    const int64_t obase = !valid ? 0 : ogeom ? seg0 + (lp / a.oinner) * a.oouter + (lp % a.oinner) * a.oistep : base;
-    const E *__restrict__ gin = (const E *)a.in + base;
-    E *__restrict__ gout = (E *)a.out + obase;
+    const uint32_t p = ((uint32_t)tile * P + pp) * (PAIR ? 2 : 1);   // (first) pencil of this thread
+    const bool valid = active && p < (uint32_t)a.npencils;
+    const PencilAt at = valid ? pencil_at(a, p) : PencilAt{0u, 0u};
+    const int64_t seg0 = a.seg_off && valid ? a.seg_off[at.seg] : 0;
+    const int64_t base = valid ? seg0 + pencil_base<CONTIG>(a, at.local) : 0;
+    const bool ogeom = !CONTIG && a.ostride != 0;
+    const int64_t obase = !valid ? 0 : ogeom ? seg0 + pencil_obase(a, at.local) : base;
+    const int64_t S = CONTIG ? 1 : a.stride;
+    const int64_t OS = CONTIG ? 1 : ogeom ? a.ostride : a.stride;
+    // of row t: the rows t + T u + q N/R lie a uniform distance further
+    const E *__restrict__ gin = (const E *)a.in + (base + t * S);
+    E *__restrict__ gout = (E *)a.out + (obase + t * OS);
     const TW *__restrict__ tw = (const TW *)a.tw;
-    const int64_t S = a.stride;
-    const int64_t OS = ogeom ? a.ostride : a.stride;
     V *row = lds + (active ? pp : 0) * LS;
 
     V v[M];
@@ -600,13 +636,13 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
             gtab[i] = evol_factor<R>(c, k * k);
         }
         if (valid) {
-            const int64_t pa = p / a.ev_d, pb = p % a.ev_d;
-            const double ka = (double)signed_k(pa, a.ev_la), kb = (double)signed_k(pb, a.ev_lb);
+            const uint32_t pa = p / (uint32_t)a.ev_d, pb = p - pa * (uint32_t)a.ev_d;
+            const double ka = (double)signed_k((int)pa, a.ev_la), kb = (double)signed_k((int)pb, a.ev_lb);
             gab = evol_factor<R>(c, ka * ka + kb * kb);
         }
         __syncthreads();
     };
-    if constexpr (CONTIG && !MULTI) {
+    if constexpr (OWN && CONTIG && !MULTI) {
         if (a.evolve) evolve_factors(a.ev_c);
     }
 
@@ -620,13 +656,13 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
             const int b = t + T * u;
             if (NBF0 % T == 0 || b < NBF0) {
 #pragma unroll
-                for (int q = 0; q < R0; q++) v[u * R0 + q] = ld_v<NTA, V>(gin + (int64_t)(b + q * NBF0) * S);
+                for (int q = 0; q < R0; q++) v[u * R0 + q] = ld_v<NTA, V>(gin + (int64_t)(T * u + q * NBF0) * S);
             }
         }
     };
     // the tile is one block of memory (uniform): pencils back to back
-    constexpr bool STAGE = STAGE_OK && Cfg::block(NT && nt_load<V, CONTIG>());
-    [[maybe_unused]] const bool block = STAGE && !a.seg_off && !ogeom && a.inner == 1 && a.outer == N && S == 1;
+    constexpr bool STAGE = OWN && Cfg::block(NT && nt_load<V, CONTIG>());
+    [[maybe_unused]] const bool block = STAGE && !a.seg_off && a.outer == N;
     [[maybe_unused]] const int64_t block0 = tile * P * N;   // its first element, and its length
     [[maybe_unused]] const int block_n = (int)(a.npencils - tile * P < P ? a.npencils - tile * P : P) * N;
     using LdsT = typename Cfg::LdsT;
@@ -642,7 +678,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
             block_to_rows<Cfg, N>(lin, v, tid, t, (LdsT *)lds, (LdsT *)lds + pp * LS);
         }
     } else if (valid && !MX_IN) {
-        if (a.gen) {
+        if (OWN && a.gen) {
 #pragma unroll
             for (int u = 0; u < U0; u++) {
                 const int b = t + T * u;
@@ -682,7 +718,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
         constexpr int NBF = NBF0;
         constexpr int U = U0;
         if (valid && !MX_IN) {
-            if constexpr (CONTIG) {
+            if constexpr (OWN && CONTIG) {
                 if (a.evolve) {
 #pragma unroll
                     for (int u = 0; u < U; u++) {
@@ -700,14 +736,15 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
             }
             // pre-twiddle after the conjugation: an inverse is conj(DFT(conj(x))) as a whole
             if (a.ptw) {
+                const TW *pt = (const TW *)a.ptw + (base - seg0 + t * S);
 #pragma unroll
                 for (int u = 0; u < U; u++) {
                     const int b = t + T * u;
                     if (NBF % T == 0 || b < NBF) {
 #pragma unroll
                         for (int q = 0; q < R0; q++) {
-                            const int64_t o = (base - seg0) + (int64_t)(b + q * NBF) * S;
-                            v[u * R0 + q] = pre_twiddle(v[u * R0 + q], o, a.istep, a.ptw);
+                            const int64_t o = (int64_t)(T * u + q * NBF) * S;
+                            v[u * R0 + q] = pre_twiddle(v[u * R0 + q], o, a.istep, pt);
                         }
                     }
                 }
@@ -839,6 +876,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                 // the previous stage's outputs for the next round's writes)
                 constexpr int Rp = GP.g[s - 1];
                 constexpr int Nsp = GP.ns[s - 1];
+                constexpr bool G0P = Nsp == 1 && Rp == 16;   // a butterfly's outputs are one group of 16
                 constexpr int NBFp = N / Rp;
                 constexpr int Up = (NBFp + T - 1) / T;
                 R *rrow = (R *)lds + (active ? pp : 0) * LS;
@@ -849,9 +887,11 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                         const int b = t + T * u;
                         if (NBFp % T == 0 || b < NBFp) {
                             const int idx = (b / Nsp) * Nsp * Rp + (b % Nsp);
-#pragma unroll
-                            for (int q = 0; q < Rp; q++)
-                                rrow[lds_pos(idx + group_out(RP, GP.first[s - 1], GP.nst[s - 1], q))] = part ? v[u * Rp + q].y : v[u * Rp + q].x;
+                            static_for<0, Rp>([&](auto qc) {
+                                constexpr int q = decltype(qc)::value;
+                                rrow[lds_pos_plus<group_out(RP, GP.first[s - 1], GP.nst[s - 1], q), G0P>(idx)] =
+                                    part ? v[u * Rp + q].y : v[u * Rp + q].x;
+                            });
                         }
                     }
                     __syncthreads();
@@ -859,11 +899,11 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                     for (int u = 0; active && u < U; u++) {
                         const int b = t + T * u;
                         if (NBF % T == 0 || b < NBF) {
-#pragma unroll
-                            for (int q = 0; q < Rr; q++) {
-                                if constexpr (part) v[u * Rr + q].y = rrow[lds_pos(b + q * NBF)];
-                                else v[u * Rr + q].x = rrow[lds_pos(b + q * NBF)];
-                            }
+                            static_for<0, Rr>([&](auto qc) {
+                                constexpr int q = decltype(qc)::value;
+                                if constexpr (part) v[u * Rr + q].y = rrow[lds_pos_plus<q * NBF>(b)];
+                                else v[u * Rr + q].x = rrow[lds_pos_plus<q * NBF>(b)];
+                            });
                         }
                     }
                     __syncthreads();
@@ -874,6 +914,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                     // exchange: write the previous stage's outputs
                     constexpr int Rp = GP.g[s - 1];
                     constexpr int Nsp = GP.ns[s - 1];
+                constexpr bool G0P = Nsp == 1 && Rp == 16;   // a butterfly's outputs are one group of 16
                     constexpr int NBFp = N / Rp;
                     constexpr int Up = (NBFp + T - 1) / T;
 #pragma unroll
@@ -881,8 +922,10 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                         const int b = t + T * u;
                         if (NBFp % T == 0 || b < NBFp) {
                             const int idx = (b / Nsp) * Nsp * Rp + (b % Nsp);
-#pragma unroll
-                            for (int q = 0; q < Rp; q++) row[lds_pos(idx + group_out(RP, GP.first[s - 1], GP.nst[s - 1], q))] = v[u * Rp + q];
+                            static_for<0, Rp>([&](auto qc) {
+                                constexpr int q = decltype(qc)::value;
+                                row[lds_pos_plus<group_out(RP, GP.first[s - 1], GP.nst[s - 1], q), G0P>(idx)] = v[u * Rp + q];
+                            });
                         }
                     }
                     __syncthreads();
@@ -892,8 +935,10 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                 for (int u = 0; active && u < U; u++) {
                     const int b = t + T * u;
                     if (NBF % T == 0 || b < NBF) {
-#pragma unroll
-                        for (int q = 0; q < Rr; q++) v[u * Rr + q] = row[lds_pos(b + q * NBF)];
+                        static_for<0, Rr>([&](auto qc) {
+                            constexpr int q = decltype(qc)::value;
+                            v[u * Rr + q] = row[lds_pos_plus<q * NBF>(b)];
+                        });
                     }
                 }
                 __syncthreads();
@@ -939,7 +984,8 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                 if (NBF % T == 0 || b < NBF) {
 #pragma unroll
                     for (int q = 0; q < RL; q++) {
-                        const int pos = b + group_out(RP, GP.first[NST - 1], GP.nst[NST - 1], q);
+                        // of the butterfly's first output, row b = t + T u
+                        const int pos = T * u + group_out(RP, GP.first[NST - 1], GP.nst[NST - 1], q);
                         V o = v[u * RL + q];
                         if (a.inv) o = cconj(o);
                         if (a.scale != 1.0) o = cscale(o, sc);
@@ -1034,7 +1080,7 @@ __global__ void __launch_bounds__((PassCfg<V, N, CONTIG, MX, NT>::THREADS), (Pas
     FB_OCCUPANCY fft_pass(PassArgs a)
 {
     using Cfg = PassCfg<V, N, CONTIG, MX, NT>;
-    __shared__ typename Cfg::LdsT lds[Cfg::P * Cfg::LS];
+    __shared__ typename Cfg::LdsT lds[Cfg::lds_elems(NT && nt_load<V, CONTIG>())];
     __shared__ real_t<V> gtab[CONTIG ? N : 1];
     pass_tile<V, N, CONTIG, MX, false, NT, true>(a, tile_of_block<xcd_remap<V, N, CONTIG, MX, NT>()>(blockIdx.x, gridDim.x),
                                            threadIdx.x, (V *)lds, gtab);

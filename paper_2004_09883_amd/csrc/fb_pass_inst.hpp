@@ -13,6 +13,7 @@ hipError_t launch_pass(const PassArgs &a, hipStream_t st)
 {
     using Cfg = PassCfg<V, N, CONTIG, MX, NT>;
     constexpr int64_t UNIT = std::is_same<V, c2x>::value ? 2 : 1;   // pencils per tile slot
+    if (!pass_args_ok(a, CONTIG)) return hipErrorInvalidValue;
     const int64_t blocks = (a.npencils + UNIT * Cfg::P - 1) / (UNIT * Cfg::P);
     if (blocks <= 0) return hipSuccess;
     hipLaunchKernelGGL((fft_pass<V, N, CONTIG, MX, NT>), dim3((unsigned)blocks), dim3(Cfg::THREADS), 0, st, a);
@@ -93,6 +94,7 @@ template <bool B3> PassInfo find_pass_pair_t(int n, bool mx)
 template <typename V, int N, bool MX, bool NT = false> hipError_t launch_pass_multi(const PassArgs &a, hipStream_t st)
 {
     using Cfg = PassCfg<V, N, true, MX, NT>;
+    if (!pass_args_ok(a, true)) return hipErrorInvalidValue;
     const int64_t blocks = (a.npencils + Cfg::P - 1) / Cfg::P;
     if (blocks <= 0) return hipSuccess;
     hipLaunchKernelGGL((fft_pass_multi<V, N, MX, NT>), dim3((unsigned)blocks), dim3(Cfg::THREADS), 0, st, a);

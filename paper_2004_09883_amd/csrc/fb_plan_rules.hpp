@@ -306,10 +306,17 @@ constexpr int wide_pencils(int n, int threads, int elems)
 // LDS, and one tile may take most of a CU's.  Measured on grids above 192 MiB
 // (narrow -> wide, us): 576 points 180 -> 146, 768: 262 -> 210, 1024: 361 ->
 // 270, 1458: 478 -> 194, 2048: 723 -> 306, 4096: 1300 -> 455.  Grids that the
-// last-level cache holds gain past 2048 points only (64 MiB: 2304 28.2 -> 22.5,
-// 4096 43.8 -> 40.6, but 1024 26.1 -> 39.4 and 768 22.6 -> 26.1), so shorter
-// passes are wide in their non-temporal instance (nt) alone.
-constexpr bool wide_strided(int n, bool contig, bool nt) { return FB_SPLIT_EXCHANGE && !contig && n > (nt ? 512 : 2048); }
+// last-level cache holds gain from 2048 points on, and from 1152 where a thread
+// holds few elements (64 MiB: 1458 25.3 -> 23.5, 2048 35 -> 31, 2304 28.2 ->
+// 22.5, 4096 43.8 -> 40.6, but 1024 26.1 -> 39.4, 1536 27.6 -> 29.3, 1944 31.8 ->
+// 34.3); the others are wide in their non-temporal instance (nt) alone.
+constexpr bool wide_strided(int n, bool contig, bool nt)
+{
+    if (!FB_SPLIT_EXCHANGE || contig) return false;
+    if (nt || n >= 2048) return n > 512;
+    return n > 1024 && grouped(n, contig, false) && group_plan(n, true).elems <= 18;
+}
+
 // Whether a complex128 pass exchanges real and imaginary parts in two rounds:
 // up to 256 points it lets more tiles share a CU (at 257 .. 512 points one
 // round was faster, the 512-point x pass 196 against 215 us), and the wide
