@@ -132,8 +132,9 @@ __device__ __forceinline__ void mx_stage16(const float2 *__restrict__ tw, const 
                 // (each form where it keeps the results that the stage always had)
                 if (q > 0) {
                     const float2 w = tw[TWOFF + (q - 1) * Ns + (b % Ns)];
-                    constexpr RadixPlan RP = radix_plan(N);
-                    v = G == 4 && RP.r[RP.count - 1] != 2 ? cmul(v, w) : mx_cmul(v, w);
+                    constexpr int LAST = radix_plan(N).r[radix_plan(N).count - 1];
+                    if constexpr (G == 4 && LAST != 2) v = cmul(v, w);
+                    else v = mx_cmul(v, w);
                 }
             }
             x[gi][i] = v;
