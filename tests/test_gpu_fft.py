@@ -135,6 +135,9 @@ def test_grouped_stages_part_filled_tiles(shape, dtype):
 
 @pytest.mark.parametrize("shape,dtype", [((1, 1, 8), fb.FB_C64), ((3, 243, 16), fb.FB_C64), ((1, 81, 27), fb.FB_C128),
                                          ((9, 9, 48), fb.FB_C128), ((2, 27, 36), fb.FB_C64_SPLITBF16),
+                                         # 256 tiles and more
+                                         ((243, 324, 16), fb.FB_C64), ((96, 243, 27), fb.FB_C128),
+                                         ((81, 162, 48), fb.FB_C128), ((243, 243, 36), fb.FB_C64_SPLITBF16),
                                          # above 192 MiB: non-temporal accesses
                                          ((243, 243, 216), fb.FB_C128), ((486, 324, 162), fb.FB_C64)])
 def test_tiles_moved_as_one_block(shape, dtype):
