@@ -249,8 +249,9 @@ const char *fb_batch_describe(const fb_batch *b);
  * only in place; it may be NULL otherwise.  persistent = 0: one launch per
  * group; 1: the whole batch in one launch (when every two-pass and 2D
  * transform's tiles lie within that transform, which fb_batch_describe
- * reports as onelaunch=1; otherwise as 2); 2: one persistent launch per
- * phase.  All three give the same bits. */
+ * reports as onelaunch=1, and no workgroup's share exceeds the mean by more
+ * than a quarter, reported as balance; otherwise as 2); 2: one persistent
+ * launch per phase.  All three give the same bits. */
 fb_status fb_batch_exec(const fb_batch *b, const void *in, void *out, void *workspace, size_t workspace_bytes,
                         int dir, int persistent, void *hip_stream);
 

@@ -1342,7 +1342,7 @@ fb_status fb_batch_exec(const fb_batch *b, const void *in, void *out, void *work
     bufs.p[2] = mid;
     bufs.inv = dir > 0;
     bufs.nt = (double)b->total * 8.0 >= (double)FB_NT_MIN_BYTES ? 1 : 0;
-    if (persistent == 1 && b->onelaunch) {
+    if (persistent == 1 && b->onelaunch && b->ol_balance <= FB_BATCH_MAX_BALANCE) {
         e = timed_launch("batch_onelaunch<c64>", 0.0, st, [&] {
             return fb::launch_batch_onelaunch(b->groups_dev, b->items_dev, b->item_begin_dev, b->ol_nblocks,
                                               b->ol_lds_bytes, bufs, st);

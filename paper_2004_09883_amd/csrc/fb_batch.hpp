@@ -9,6 +9,15 @@ namespace fb {
 
 #define FB_BATCH_MAX_GROUPS 512
 
+// Largest load of a workgroup, over the mean load, at which a batch runs in
+// one launch.  A two-pass transform is one workgroup's work there, so a batch
+// whose longest transform outweighs an even share waits for it; one launch per
+// phase spreads its tiles over the device.  Measured (one launch / per phase,
+// us): 4096 + 64 transforms, balance 1.01: 1108 / 1119; 3000 + 10, 1.08: 725 /
+// 736; 2048 + 64, 1.69: 695 / 656; 1024 + 30, 3.5: 578 / 329; 128 + 32, 15.9:
+// 450 / 56; 64, 48: 449 / 35.
+#define FB_BATCH_MAX_BALANCE 1.25
+
 // One (length, pass) group of a batch.  The data pointers of `args` are
 // chosen per execution: in_sel / out_sel name the buffer (0 = the caller's
 // input, 1 = the caller's output, 2 = the workspace data region).

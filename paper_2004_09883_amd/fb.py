@@ -416,7 +416,8 @@ def fb_batch_exec(batch: Batch, x_in, x_out, workspace, direction: int = FB_FORW
     """x_in/x_out: complex64 device tensors of batch.elements values; workspace:
     a device tensor (uint8) of at least batch.workspace_bytes(x_in is x_out).
     persistent: False/0 one launch per group, True/1 the whole batch in one
-    launch, 2 one persistent launch per phase."""
+    launch (per phase where one transform outweighs an even share), 2 one
+    persistent launch per phase."""
     for t, name in ((x_in, "in"), (x_out, "out")):
         if not isinstance(t, int) and (t.numel() != batch.elements or not t.is_contiguous()):
             raise FbError(FB_ERR_INVALID_ARG, f"{name} must be a contiguous tensor of {batch.elements} elements")

@@ -134,3 +134,21 @@ def test_batch_edge_shapes(lens, n2d, side):
             assert e < TOL, (persistent, i, n, e)
         outs.append(got)
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("lens,n2d,side", [([196608], 0, 0), ([256] * 7 + [98304], 2, 64), ([4096] * 3, 0, 0)])
+def test_unbalanced_batch_equals_per_group_bitwise(lens, n2d, side):
+    """Batches whose longest transform outweighs an even share of the device
+    run mode 1 phase by phase: the bits of the other modes, in and out of
+    place, both directions."""
+    batch = fb.Batch(lens, n2d=n2d, side2d=side)
+    balance = float(batch.description.split("balance=")[1].split()[0])
+    assert balance > 1.25, batch.description
+    x = packed_input(batch, 9)
+    for in_place in (False, True):
+        for direction in (fb.FB_FORWARD, fb.FB_INVERSE):
+            a = run(batch, x, direction, 0, in_place)
+            assert np.array_equal(a, run(batch, x, direction, 1, in_place)), (in_place, direction)
+    i = len(lens) - 1
+    o = batch.offsets[i]
+    assert rel_l2(a[o:o + lens[i]].astype(np.complex128), ref_transform(batch, x, i, fb.FB_INVERSE)) < TOL
