@@ -553,126 +553,91 @@ struct StripShared {
     double slot[2 * LU_NB][LU_NB];       // the touched rows' contents, by composed index
     int64_t dst[2 * LU_NB], src[2 * LU_NB];
     int np;
-    int16_t send[LU_MAX_N], recv[LU_MAX_N];   // per row from k: the slot it sends / receives, or -1
-    double stage[LU_PANEL_THREADS * LU_STAGE_LD];   // one register slot's strip rows on their way in
+    int16_t recv[LU_MAX_N];              // per row from k: the slot whose content it takes, or -1
+    double stage[LU_PANEL_THREADS * LU_STAGE_LD];   // one register slot's rows on their way to their threads
 };
 
-// Columns [c0, c0 + w) of rows k .. n-1 after panel k: thread t holds rows
-// k + t + LU_PANEL_THREADS r in v[r][0 .. w).  keep: store only the U12 rows
-// and leave the rows below them, updated, in v.
-template <int R>
+// Columns [c0, c0 + w) of rows k .. n-1 after panel k.  KEEP: store only the
+// U12 rows and leave the rows below them, updated, in v (thread t holds rows
+// k + t + LU_PANEL_THREADS r in v[r][0 .. w)); otherwise store every row.
+//
+// Bound: the latency and the cache-line lookups of one CU's loads, since a
+// strip is one workgroup's work.  So A22 -= L21 U12 runs on the binary64 matrix
+// cores (as in lu_gemm_mfma: 16-row blocks, lane l holds rows 4 r + l / 16 of
+// column l mod 16), whose operands load and store without passing through
+// LDS: an access of A22 covers 4 whole rows and one of L21 16 rows' 32 bytes,
+// where a row per lane covers 64 lines.  The rows that the exchanges touch (at
+// most 2 LU_NB) are loaded apart, after the permutation is known: the first
+// LU_NB of them are U12's right-hand sides, the others are updated by one
+// thread per element and replace what the blocks computed in their place.
+// Elements are updated in column order, so the factors are bitwise those of a
+// row per lane on the vector units.  Measured: XXSTRIP
+template <bool KEEP, int R>
 __device__ __forceinline__ void strip_update(double *__restrict__ a, int64_t n, int64_t lda, int64_t k, int nb,
-                                             const int32_t *__restrict__ ipiv, int64_t c0, int w, bool keep,
+                                             const int32_t *__restrict__ ipiv, int64_t c0, int w,
                                              double (&v)[LU_ROWS][LU_NB], StripShared &sh)
 {
     static_assert(2 * LU_NB <= 64, "one wave composes the permutation");
-    static_assert(LU_NB * LU_NB <= LU_PANEL_THREADS, "one L11 element per thread");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    static_assert(2 * LU_NB * LU_NB == LU_PANEL_THREADS && LU_NB == 16, "one touched element per thread");
+    constexpr int BLOCKS = 4;   // 16-row blocks of a wave's 64 rows of one register slot
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = (int)(n - k);
-    // ---- every load that does not depend on the permutation goes first:
-    // the strip's first rows, the first half of L21, L11 and the pivots.
-    // Every load is unconditional (rows past the end read the last row
-    // again: they are never stored, published or used as candidates), so
-    // that no load waits at a branch.  A strip is called with nb == LU_NB (a
-    // panel is followed by columns only when it is whole) and m > nb.
-    //
-    // The strip's rows go through LDS one register slot (512 rows) at a time:
-    // a wavefront's load covers 8 rows (8 lanes per 128-byte row, two
-    // adjacent doubles per lane) instead of 64 rows when every lane reads
-    // its own row, which costs the load pipeline 8 times the cache-line
-    // lookups (on one 2048 x 16 panel, 26-33 thousand cycles against 12.7).
-    double g[2 * 8];
-    auto load_slot = [&](auto rc) {
-        constexpr int r = decltype(rc)::value;
-#pragma unroll
-        for (int u = 0; u < 8; u++) {
-            const int e = tid + LU_PANEL_THREADS * u, row = e >> 3, ch = e & 7;
-            const int i = LU_PANEL_THREADS * r + row, ic = i < m ? i : m - 1;
-            const int c0c = 2 * ch < w ? 2 * ch : w - 1, c1c = 2 * ch + 1 < w ? 2 * ch + 1 : w - 1;
-            g[2 * u] = a[(k + ic) * lda + c0 + c0c];
-            g[2 * u + 1] = a[(k + ic) * lda + c0 + c1c];
-        }
-    };
-    load_slot(std::integral_constant<int, 0>{});
-    // L21, four panel columns per quarter, two quarters in flight: each lane
-    // reads its own rows' 32 bytes (the second pair of quarters is read
-    // during the first pair's products)
-    double lq[2][LU_ROWS][4];
-    auto load_quarter = [&](auto qc, double (&dq)[LU_ROWS][4]) {
-        constexpr int q = decltype(qc)::value;
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-            const int i = tid + LU_PANEL_THREADS * r, ic = i < nb ? nb : (i < m ? i : m - 1);   // rows of L21
-#pragma unroll
-            for (int t = 0; t < 4; t++) dq[r][t] = a[(k + ic) * lda + k + 4 * q + t];
-        }
-    };
-    load_quarter(std::integral_constant<int, 0>{}, lq[0]);
-    load_quarter(std::integral_constant<int, 1>{}, lq[1]);
-    const int li = (tid / LU_NB) % LU_NB, lj = tid % LU_NB;
-    const double lv = a[(k + (li < nb ? li : 0)) * lda + k + (lj < nb ? lj : 0)];   // clamped: every thread loads
+    const int li = lane & 15, lk = lane >> 4;
+    const int q = tid >> 4, c = tid & 15;   // this thread's element of the touched rows
+    const int cc = c < w ? c : w - 1;       // (columns past the strip read its last one and are not stored)
+    const int lc = li < w ? li : w - 1;
+    // ---- the pivots, L11, and the first rows' blocks: every load that does
+    // not depend on the permutation.  Rows past the end read the last row
+    // again and are not stored.  A strip is called with nb == LU_NB (a panel is
+    // followed by columns only when it is whole).
     const int32_t pv32 = ipiv[k + (lane < nb ? lane : 0)];
-    // ---- the permutation, composed by wave 0, as maps over the rows
+    const double lv = a[(k + (q & 15)) * lda + k + c];   // threads 256.. read L11 again
+    auto row_of = [&](int i) { return a + (k + (i < m ? i : m - 1)) * lda; };
+    lu_d4 acc[BLOCKS];
+    double la[BLOCKS][4];
+    auto load_slot = [&](int r) {
 #pragma unroll
-    for (int r = 0; r < R; r++) {
-        const int i = tid + LU_PANEL_THREADS * r;
-        if (i < m) {
-            sh.send[i] = -1;
-            sh.recv[i] = -1;
+        for (int b = 0; b < BLOCKS; b++) {
+            const int i0 = LU_PANEL_THREADS * r + 64 * wave + 16 * b;
+#pragma unroll
+            for (int t = 0; t < 4; t++) acc[b][t] = row_of(i0 + 4 * t + lk)[c0 + lc];
+            const double *lr = row_of(i0 + li) + k + lk;
+#pragma unroll
+            for (int t = 0; t < 4; t++) la[b][t] = lr[4 * t];
         }
+    };
+    load_slot(0);
+    // ---- the permutation, composed by wave 0
+    if constexpr (KEEP) {
+        for (int i = tid; i < m; i += LU_PANEL_THREADS) sh.recv[i] = -1;
     }
-    if (tid < LU_NB * LU_NB) sh.L[li][lj] = (li < nb && lj < nb) ? lv : 0.0;
+    if (tid < LU_NB * LU_NB) sh.L[q][c] = lv;
     int64_t d = -1, sr = -1;
     int cnt = 0;
-    if (wave == 0) cnt = compose_perm(lane < nb ? (int64_t)pv32 : 0, k, nb, lane, d, sr);
-    static_for<0, R>([&](auto rc) {
-        constexpr int r = decltype(rc)::value;
-        if (r > 0) __syncthreads();   // the previous slot has been read
-#pragma unroll
-        for (int u = 0; u < 8; u++) {
-            const int e = tid + LU_PANEL_THREADS * u, row = e >> 3, ch = e & 7;
-            sh.stage[row * LU_STAGE_LD + 2 * ch] = g[2 * u];
-            sh.stage[row * LU_STAGE_LD + 2 * ch + 1] = g[2 * u + 1];
+    if (wave == 0) {
+        cnt = compose_perm(lane < nb ? (int64_t)pv32 : 0, k, nb, lane, d, sr);
+        if (lane < cnt) {
+            sh.dst[lane] = d;
+            sh.src[lane] = sr;
         }
-        if constexpr (r + 1 < R) load_slot(std::integral_constant<int, r + 1>{});
-        __syncthreads();   // (the first also orders the maps' initialisation and L11)
-#pragma unroll
-        for (int c = 0; c < LU_NB; c++) v[r][c] = sh.stage[tid * LU_STAGE_LD + c];
-    });
-    if (wave == 0 && lane < cnt) {
-        sh.send[sr - k] = (int16_t)lane;
-        sh.recv[d - k] = (int16_t)lane;
+        if (lane == 0) sh.np = cnt;
     }
     __syncthreads();
-    // ---- the exchanges: the holders of the source rows publish them, the
-    // holders of the destination rows take them
+    const int np = sh.np;
+    const int64_t dq = q < np ? sh.dst[q] : k, sq = q < np ? sh.src[q] : k;
+    double p = a[sq * lda + c0 + cc];
+    double lrow[LU_NB];   // L21 of the touched row below U12
 #pragma unroll
-    for (int r = 0; r < R; r++) {
-        const int i = tid + LU_PANEL_THREADS * r;
-        const int q = i < m ? sh.send[i] : -1;
-        if (q >= 0) {
-#pragma unroll
-            for (int c = 0; c < LU_NB; c++) sh.slot[q][c] = v[r][c];
-        }
+    for (int j = 0; j < LU_NB; j++) lrow[j] = q >= nb ? a[dq * lda + k + j] : 0.0;
+    if constexpr (KEEP) {
+        if (wave == 0 && lane >= nb && lane < cnt) sh.recv[d - k] = (int16_t)lane;
     }
+    if (q < nb) sh.U[q][c] = p;
+    asm volatile("" : "+v"(p));   // every touched row has arrived before a wave stores its blocks
     __syncthreads();
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-        const int i = tid + LU_PANEL_THREADS * r;
-        const int q = i < m ? sh.recv[i] : -1;
-        if (q >= 0) {
-#pragma unroll
-            for (int c = 0; c < LU_NB; c++) v[r][c] = sh.slot[q][c];
-        }
-    }
-    // ---- U12 = L11^-1 A12: rows k .. k+nb-1 are rows r = 0 of threads
-    // 0 .. nb-1; one thread per column solves in registers
+    // ---- U12 = L11^-1 A12, one thread per column
     if (tid < LU_NB) {
-#pragma unroll
-        for (int c = 0; c < LU_NB; c++) sh.U[tid][c] = tid < nb ? v[0][c] : 0.0;
-    }
-    __syncthreads();
-    if (tid < w) {
         double col[LU_NB];
 #pragma unroll
         for (int i = 0; i < LU_NB; i++) col[i] = sh.U[i][tid];
@@ -685,44 +650,71 @@ __device__ __forceinline__ void strip_update(double *__restrict__ a, int64_t n, 
         for (int i = 0; i < LU_NB; i++) sh.U[i][tid] = col[i];
     }
     __syncthreads();
-    // ---- A22 -= L21 U12, the panel's columns in order (on every row held:
-    // the U12 rows, which read some row of L21, are restored afterwards;
-    // rows past the end are never stored)
-    static_for<0, 4>([&](auto qc) {
-        constexpr int q = decltype(qc)::value;
-        static_for<0, 4>([&](auto tc) {
-            constexpr int t = decltype(tc)::value, j = 4 * q + t;
-            if (j < nb) {   // uniform
-                double u[LU_NB];
+    // ---- the touched rows
+    if (q < nb) {
+        p = sh.U[q][c];
+    } else {
 #pragma unroll
-                for (int c = 0; c < LU_NB; c++) u[c] = sh.U[j][c];
+        for (int j = 0; j < LU_NB; j++) p = fma(-lrow[j], sh.U[j][c], p);
+        if constexpr (KEEP) sh.slot[q][c] = p;
+    }
+    // ---- A22 -= L21 U12
+    double bu[4];
 #pragma unroll
-                for (int r = 0; r < R; r++) {
+    for (int t = 0; t < 4; t++) bu[t] = sh.U[4 * t + lk][li];
+    static_for<0, R>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
 #pragma unroll
-                    for (int c = 0; c < LU_NB; c++) v[r][c] -= lq[q & 1][r][t] * u[c];
+        for (int b = 0; b < BLOCKS; b++) {
+#pragma unroll
+            for (int t = 0; t < 4; t++)
+                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-la[b][t], bu[t], acc[b], 0, 0, 0);
+        }
+        if constexpr (KEEP) {
+            // to the rows' threads, which are lanes of the same wave
+            double *st = sh.stage + 64 * wave * LU_STAGE_LD;
+#pragma unroll
+            for (int b = 0; b < BLOCKS; b++) {
+#pragma unroll
+                for (int t = 0; t < 4; t++) st[(16 * b + 4 * t + lk) * LU_STAGE_LD + li] = acc[b][t];
+            }
+            if constexpr (r + 1 < R) load_slot(r + 1);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int j = 0; j < LU_NB; j++) v[r][j] = st[lane * LU_STAGE_LD + j];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        } else {
+#pragma unroll
+            for (int b = 0; b < BLOCKS; b++) {
+                const int i0 = LU_PANEL_THREADS * r + 64 * wave + 16 * b;
+#pragma unroll
+                for (int t = 0; t < 4; t++) {
+                    const int i = i0 + 4 * t + lk;
+                    if (i >= nb && i < m && li < w) a[(k + i) * lda + c0 + li] = acc[b][t];
                 }
             }
-        });
-        if constexpr (q + 2 < 4) load_quarter(std::integral_constant<int, q + 2>{}, lq[q & 1]);
+            if constexpr (r + 1 < R) load_slot(r + 1);
+        }
     });
-    if (tid < nb) {
+    // ---- the touched rows' own values over what the blocks put in their place
+    if constexpr (KEEP) {
+        __syncthreads();   // the slots are written
 #pragma unroll
-        for (int c = 0; c < LU_NB; c++) v[0][c] = sh.U[tid][c];
-    }
-    // ---- store
+        for (int r = 0; r < R; r++) {
+            const int i = tid + LU_PANEL_THREADS * r;
+            const int s = i < m ? sh.recv[i] : -1;
+            if (s >= 0) {
 #pragma unroll
-    for (int r = 0; r < R; r++) {
-        const int i = tid + LU_PANEL_THREADS * r;
-        if (i < m && (!keep || i < nb)) {
-            if (w == LU_NB) {
-#pragma unroll
-                for (int c = 0; c < LU_NB; c++) a[(k + i) * lda + c0 + c] = v[r][c];
-            } else {
-#pragma unroll
-                for (int c = 0; c < LU_NB; c++)
-                    if (c < w) a[(k + i) * lda + c0 + c] = v[r][c];
+                for (int j = 0; j < LU_NB; j++) v[r][j] = sh.slot[s][j];
             }
         }
+        if (q < nb && c < w) a[(k + q) * lda + c0 + c] = p;
+    } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the blocks' stores come first
+        __syncthreads();
+        if (q < np && c < w) a[dq * lda + c0 + c] = p;
     }
 }
 
@@ -773,7 +765,7 @@ __global__ void __launch_bounds__(LU_PANEL_THREADS)
     const int nb2 = (int)(n - s < LU_NB ? n - s : LU_NB);   // the next panel's width (when s < n)
     if (b < nfirst) {
         double v[LU_ROWS][LU_NB];
-        strip_update<R>(a, n, lda, k, nb, ipiv, s, nb2, true, v, ss);
+        strip_update<true, R>(a, n, lda, k, nb, ipiv, s, nb2, v, ss);
         // rows k + nb .. n-1 are the next panel's rows 0 .. n-s-1; the U12
         // rows above them are done
         const int m = (int)(n - k);
@@ -792,7 +784,7 @@ __global__ void __launch_bounds__(LU_PANEL_THREADS)
         const int64_t c0 = s + nb2 + (int64_t)LU_NB * (b - nfirst);
         const int w = (int)(n - c0 < LU_NB ? n - c0 : LU_NB);
         double v[LU_ROWS][LU_NB];
-        strip_update<R>(a, n, lda, k, nb, ipiv, c0, w, false, v, ss);
+        strip_update<false, R>(a, n, lda, k, nb, ipiv, c0, w, v, ss);
     } else {
         for (int t = 0; nfirst && t < FB_LU_STRIP_DELAY * R; t++) __builtin_amdgcn_s_sleep(127);
         left_swaps(a, lda, k, nb, ipiv, (int64_t)LU_PANEL_THREADS * (b - nfirst - nstrips), ss);
