@@ -126,10 +126,43 @@ struct PanelShared {
     double crow[2][LU_W][LU_NB];
 };
 
+// A wave's 64 rows of one register slot between memory and the rows' threads,
+// through the wave's part of the stage: 16 lanes move one row's 128 bytes, so
+// an access covers 4 rows instead of the 64 of a row per lane (the first
+// panel of 2048 rows 48.2 -> 36.5 us; 2048 x 2048 4.65 -> 4.59 ms; 333 x 333, one
+// register slot, 424 -> 434 us, so its rows are stored by their threads).
+constexpr int LU_STAGE_LD = LU_NB + 2;   // staged row stride in doubles: 16-byte aligned rows, spread banks
+constexpr int LU_STAGE = LU_PANEL_THREADS * LU_STAGE_LD;
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// row `lane` of the wave (v, stored at row lab of the panel when lab < m)
+__device__ __forceinline__ void store_rows(const double (&v)[LU_NB], int lab, double *__restrict__ a, int64_t lda,
+                                           int64_t k, int m, int nb, double *stage)
+{
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    double *st = stage + (threadIdx.x >> 6) * 64 * LU_STAGE_LD;
+#pragma unroll
+    for (int c = 0; c < LU_NB; c++) st[lane * LU_STAGE_LD + c] = v[c];
+    *reinterpret_cast<int *>(&st[lane * LU_STAGE_LD + LU_NB]) = lab;
+    wave_lds_order();
+#pragma unroll
+    for (int t = 0; t < 16; t++) {
+        const int row = 4 * t + lk;
+        const double x = st[row * LU_STAGE_LD + li];
+        const int l = *reinterpret_cast<const int *>(&st[row * LU_STAGE_LD + LU_NB]);
+        if (l < m && li < nb) a[(k + l) * lda + k + li] = x;
+    }
+    wave_lds_order();
+}
+
 template <bool FULL, int R>
 __device__ __forceinline__ void panel_columns(double (&v)[LU_ROWS][LU_NB], int (&lab)[LU_ROWS],
                                               double *__restrict__ a, int64_t lda, int64_t k, int m, int nb,
-                                              int32_t *__restrict__ ipiv, int32_t *__restrict__ info, PanelShared &sh)
+                                              int32_t *__restrict__ ipiv, int32_t *__restrict__ info, PanelShared &sh,
+                                              double *stage)
 {
     constexpr int W = LU_W;
     static_assert(W == 8 && LU_NB == 16, "a wave reads the W candidate rows with one 16-byte access per lane");
@@ -258,13 +291,15 @@ __device__ __forceinline__ void panel_columns(double (&v)[LU_ROWS][LU_NB], int (
         }
     });
 
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-        if (lab[r] < m) {
+    if constexpr (R == 1) {   // too few rows for the lookups to matter: one LDS round trip less
+        if (lab[0] < m) {
 #pragma unroll
             for (int c = 0; c < LU_NB; c++)
-                if (c < nb) a[(k + lab[r]) * lda + k + c] = v[r][c];
+                if (c < nb) a[(k + lab[0]) * lda + k + c] = v[0][c];
         }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; r++) store_rows(v[r], lab[r], a, lda, k, m, nb, stage);
     }
     if (tid == 0) {
 #pragma unroll
@@ -285,17 +320,31 @@ __global__ void __launch_bounds__(LU_PANEL_THREADS)
     const int tid = threadIdx.x;
     const int m = (int)(n - k);   // rows of the panel (<= LU_ROWS * LU_PANEL_THREADS, checked on the host)
     if (FULL) nb = LU_NB;
+    __shared__ double stage[LU_STAGE];
+    const int lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+    double *st = stage + wave * 64 * LU_STAGE_LD;
     double v[LU_ROWS][LU_NB];
     int lab[LU_ROWS];   // the row's position; rows past the panel keep positions >= m
+    double g[R][16];    // every row's part in flight at once; past the end the last row and column again
 #pragma unroll
     for (int r = 0; r < R; r++) {
-        const int i = tid + LU_PANEL_THREADS * r;
-        lab[r] = i;
 #pragma unroll
-        for (int c = 0; c < LU_NB; c++)
-            v[r][c] = (i < m && c < nb) ? a[(k + i) * lda + k + c] : 0.0;
+        for (int t = 0; t < 16; t++) {
+            const int i = LU_PANEL_THREADS * r + 64 * wave + 4 * t + lk;
+            g[r][t] = a[(k + (i < m ? i : m - 1)) * lda + k + (li < nb ? li : nb - 1)];
+        }
     }
-    panel_columns<FULL, R>(v, lab, a, lda, k, m, nb, ipiv, info, sh);
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        lab[r] = tid + LU_PANEL_THREADS * r;
+#pragma unroll
+        for (int t = 0; t < 16; t++) st[(4 * t + lk) * LU_STAGE_LD + li] = g[r][t];
+        wave_lds_order();
+#pragma unroll
+        for (int c = 0; c < LU_NB; c++) v[r][c] = st[lane * LU_STAGE_LD + c];
+        wave_lds_order();
+    }
+    panel_columns<FULL, R>(v, lab, a, lda, k, m, nb, ipiv, info, sh, stage);
 }
 
 // The panel's swaps (rows k+j <-> ipiv[k+j], j = 0..nb-1 in order) on every
@@ -546,7 +595,6 @@ __global__ void __launch_bounds__(256)
 // Every element receives the same operations in the same order as in
 // lu_swap_trsm and lu_gemm, so the factors are bitwise those of the
 // three-launch schedule.
-constexpr int LU_STAGE_LD = LU_NB + 2;   // staged row stride in doubles: 16-byte aligned rows, spread banks
 struct StripShared {
     double L[LU_NB][LU_NB + 1];          // L11
     double U[LU_NB][LU_NB + 1];          // the strip's U12 block
@@ -554,7 +602,7 @@ struct StripShared {
     int64_t dst[2 * LU_NB], src[2 * LU_NB];
     int np;
     int16_t recv[LU_MAX_N];              // per row from k: the slot whose content it takes, or -1
-    double stage[LU_PANEL_THREADS * LU_STAGE_LD];   // one register slot's rows on their way to their threads
+    double stage[LU_STAGE];   // one register slot's rows on their way to their threads
 };
 
 // Columns [c0, c0 + w) of rows k .. n-1 after panel k.  KEEP: store only the
@@ -571,7 +619,8 @@ struct StripShared {
 // LU_NB of them are U12's right-hand sides, the others are updated by one
 // thread per element and replace what the blocks computed in their place.
 // Elements are updated in column order, so the factors are bitwise those of a
-// row per lane on the vector units.  Measured: XXSTRIP
+// row per lane on the vector units.  2048 x 2048 4.87 -> 4.65 ms, 333 x 333 452 ->
+// 424 us.
 template <bool KEEP, int R>
 __device__ __forceinline__ void strip_update(double *__restrict__ a, int64_t n, int64_t lda, int64_t k, int nb,
                                              const int32_t *__restrict__ ipiv, int64_t c0, int w,
@@ -679,12 +728,10 @@ __device__ __forceinline__ void strip_update(double *__restrict__ a, int64_t n, 
                 for (int t = 0; t < 4; t++) st[(16 * b + 4 * t + lk) * LU_STAGE_LD + li] = acc[b][t];
             }
             if constexpr (r + 1 < R) load_slot(r + 1);
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_order();
 #pragma unroll
             for (int j = 0; j < LU_NB; j++) v[r][j] = st[lane * LU_STAGE_LD + j];
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_order();
         } else {
 #pragma unroll
             for (int b = 0; b < BLOCKS; b++) {
@@ -775,7 +822,7 @@ __global__ void __launch_bounds__(LU_PANEL_THREADS)
             const int i = threadIdx.x + LU_PANEL_THREADS * r;
             lab[r] = (i >= nb && i < m) ? i - nb : 0x3fffffff;
         }
-        panel_columns<FULL_NEXT, R>(v, lab, a, lda, s, m - nb, nb2, ipiv, info, ps);
+        panel_columns<FULL_NEXT, R>(v, lab, a, lda, s, m - nb, nb2, ipiv, info, ps, ss.stage);
     } else if (b < nfirst + nstrips) {
         // the strips have the length of the next panel's factorization to
         // finish; they start after a pause, so that workgroup 0's own loads
