@@ -71,14 +71,19 @@ __device__ __forceinline__ int64_t pencil_obase(const PassArgs &a, uint32_t loca
     return (int64_t)q * a.oouter + (int64_t)(local - q * in) * a.oistep;
 }
 
-template <typename V, int N, bool CONTIG, bool MX = false, bool NT = false> struct PassCfg {
+template <typename V, int N, bool CONTIG, bool MX = false, bool NT = false, bool MULTI = false> struct PassCfg {
     // complex128 tiles exchange real and imaginary parts in two rounds
     static constexpr bool SPLIT = std::is_same<V, double2>::value && split_exchange(N, CONTIG, NT);
     using LdsT = typename std::conditional<SPLIT, double, V>::type;   // LDS element
     static constexpr RadixPlan RP = radix_plan(N);
-    static constexpr GroupPlan GP = group_plan(N, grouped(N, CONTIG, MX));
+    // a multi-output pass holds its elements twice: in groups of more than 18
+    // complex128 elements it has too few registers (729 points, 6 steps of
+    // 486 x 36 x 729: 2.67 ms stage by stage, 3.01 in groups of 27)
+    static constexpr bool GROUPED = grouped(N, CONTIG, MX) &&
+                                    !(MULTI && std::is_same<V, double2>::value && group_plan(N, true).elems > 18);
+    static constexpr GroupPlan GP = group_plan(N, GROUPED);
     static constexpr int T = GP.threads;
-    static constexpr int P = pencils_per_wg(N, CONTIG, (int)sizeof(V), MX, SPLIT);
+    static constexpr int P = pencils_per_wg(N, CONTIG, (int)sizeof(V), MX, SPLIT, GROUPED);
     static constexpr int THREADS = P * T;
     // waves per SIMD the kernel's registers must leave room for (1: no
     // demand): two 512-thread tiles per CU for the wide strided passes (1024
@@ -579,7 +584,7 @@ __device__ __forceinline__ void rows_to_block(const V (&v)[M], V (&lin)[Cfg::LIN
 template <typename V, int N, bool CONTIG, bool MX, bool MULTI = false, bool NT = false, bool OWN = false>
 __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int tid, V *lds, real_t<V> *gtab)
 {
-    using Cfg = PassCfg<V, N, CONTIG, MX, NT>;
+    using Cfg = PassCfg<V, N, CONTIG, MX, NT, MULTI>;
     using R = real_t<V>;
     constexpr RadixPlan RP = Cfg::RP;
     constexpr GroupPlan GP = Cfg::GP;
@@ -1093,9 +1098,9 @@ __global__ void __launch_bounds__((PassCfg<V, N, CONTIG, MX, NT>::THREADS), (Pas
 // once and output j (evolution constant ev_cs[j]) is written at
 // out + j out_step, for j < nout.
 template <typename V, int N, bool MX, bool NT = false>
-__global__ void __launch_bounds__((PassCfg<V, N, true, MX, NT>::THREADS)) FB_OCCUPANCY fft_pass_multi(PassArgs a)
+__global__ void __launch_bounds__((PassCfg<V, N, true, MX, NT, true>::THREADS)) FB_OCCUPANCY fft_pass_multi(PassArgs a)
 {
-    using Cfg = PassCfg<V, N, true, MX, NT>;
+    using Cfg = PassCfg<V, N, true, MX, NT, true>;
     __shared__ typename Cfg::LdsT lds[Cfg::P * Cfg::LS];
     __shared__ real_t<V> gtab[N];
     pass_tile<V, N, true, MX, true, NT, true>(a, tile_of_block<xcd_remap<V, N, true, MX, NT>()>(blockIdx.x, gridDim.x),

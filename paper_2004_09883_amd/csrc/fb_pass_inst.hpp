@@ -93,7 +93,7 @@ template <bool B3> PassInfo find_pass_pair_t(int n, bool mx)
 
 template <typename V, int N, bool MX, bool NT = false> hipError_t launch_pass_multi(const PassArgs &a, hipStream_t st)
 {
-    using Cfg = PassCfg<V, N, true, MX, NT>;
+    using Cfg = PassCfg<V, N, true, MX, NT, true>;
     if (!pass_args_ok(a, true)) return hipErrorInvalidValue;
     const int64_t blocks = (a.npencils + Cfg::P - 1) / Cfg::P;
     if (blocks <= 0) return hipSuccess;
@@ -110,8 +110,8 @@ template <typename V, int N, bool MX> constexpr PassLauncher nt_launcher_multi()
 // exists and MX is asked for).
 template <typename V, int N> PassInfo pass_info_multi(bool mx)
 {
-    using Cfg = PassCfg<V, N, true>;
-    using CfgM = PassCfg<V, N, true, true>;
+    using Cfg = PassCfg<V, N, true, false, false, true>;
+    using CfgM = PassCfg<V, N, true, true, false, true>;
     if constexpr (mx_capable<V, N, true>()) {
         if (mx) return {&launch_pass_multi<V, N, true>, CfgM::P, CfgM::THREADS, 1, nt_launcher_multi<V, N, true>()};
     }

@@ -326,13 +326,13 @@ constexpr bool split_exchange(int n, bool contig, bool nt)
     return (FB_SPLIT_EXCHANGE && n <= FB_SPLIT_MAX_N) || wide_strided(n, contig, nt);
 }
 
-constexpr int pencils_per_wg(int n, bool contig, int esize, bool mx = false, bool split = false)
+constexpr int pencils_per_wg(int n, bool contig, int esize, bool mx = false, bool split = false, bool groups = true)
 {
     if (split && !contig && n > 512) {
         const GroupPlan gp = group_plan(n, grouped(n, contig, mx));
         return wide_pencils(n, gp.threads, gp.elems);
     }
-    if (grouped(n, contig, mx)) return grouped_pencils(n, group_plan(n, true).threads, contig, esize, split);
+    if (groups && grouped(n, contig, mx)) return grouped_pencils(n, group_plan(n, true).threads, contig, esize, split);
     if (mx) {
         const int P = pencils_per_wg_b(n, contig, esize, true, split);
         if ((P * threads_per_pencil(n)) % 64 == 0) return P;
