@@ -151,3 +151,50 @@ def test_lu_nan_and_inf_end_with_rows_of_the_matrix_as_pivots():
         a[40, 3] = bad
         _, ipiv, info, _ = gpu_lu(a)
         assert info == 0 and np.all(ipiv >= np.arange(70)) and np.all(ipiv < 70)
+
+
+@pytest.mark.parametrize("n", [64, 600, 2048])
+def test_lu_quotients_are_divisions(n):
+    """Pivot rows with nothing right of the pivot, so that L is the quotients
+    of the entries below by the pivots and nothing else: what a division
+    gives, bit for bit, for quotients from ordinary ones down to subnormal
+    ones and pivots of any exponent, the rows in any order."""
+    rng = np.random.default_rng(n)
+    h, m = n // 2, n - n // 2
+    sign = lambda shape: rng.choice([-1.0, 1.0], shape)
+    pivots = {"order 1": rng.uniform(1, 2, h) * sign(h), "all ones": (2 - 2.0**-52) * 2.0 ** rng.integers(-390, 390, h),
+              "edges": rng.uniform(1, 2, h) * sign(h) * 2.0 ** rng.integers(-405, 405, h)}
+    below = {"ordinary": rng.uniform(-1, 1, (m, h)), "2^-990": rng.uniform(1, 2, (m, h)) * 2.0**-990,
+             "2^-1021": rng.uniform(1, 2, (m, h)) * 2.0**-1021 * sign((m, h)),
+             "subnormal": rng.integers(1, 1 << 40, (m, h)) * 2.0**-1074 * sign((m, h)),
+             "any": rng.uniform(1, 2, (m, h)) * 2.0 ** rng.integers(-1074, -1, (m, h)).astype(float)}
+    for pname, piv in pivots.items():
+        for bname, u in below.items():
+            print(f"lu quotients n={n} pivots {pname} below {bname}", flush=True)
+            v = u * np.abs(piv)
+            a = np.zeros((n, n))
+            a[:h, :h], a[h:, :h], a[h:, h:] = np.diag(piv), v, np.eye(m)
+            order = rng.permutation(n)
+            lu, ipiv, info, _ = gpu_lu(a[order])
+            for j, p in enumerate(ipiv):
+                order[[j, p]] = order[[p, j]]
+            assert info == 0 and np.array_equal(order[:h], np.arange(h))
+            want = v[order[h:] - h] / piv
+            got = lu[h:, :h]
+            where = want != 0   # (the sign of a zero also depends on the updates before)
+            assert np.array_equal(got[where].view(np.int64), want[where].view(np.int64)), (pname, bname)
+
+
+@pytest.mark.parametrize("col", [0, 20])
+@pytest.mark.parametrize("n", [64, 600, 2048])
+def test_lu_quotients_of_zeros_keep_their_sign(n, col):
+    """Zeros of both signs below pivots of both signs, in the first panel and
+    in one that a strip update hands over."""
+    rng = np.random.default_rng(n + col)
+    for piv in (1.5, -1.5, -2 + 2.0**-52):
+        a = np.eye(n)
+        v = rng.choice([0.0, -0.0, 0.5, -0.25, 2.0**-1070], n - col - 1)
+        a[col, col], a[col + 1:, col] = piv, v
+        lu, _, info, _ = gpu_lu(a)
+        assert info == 0
+        assert np.array_equal(lu[col + 1:, col].copy().view(np.int64), (v / piv).view(np.int64)), piv
