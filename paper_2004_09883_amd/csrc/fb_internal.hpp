@@ -94,7 +94,15 @@ struct PassInfo {
     // the same pass with non-temporal global accesses (nullptr when the pass
     // kind has none); launched instead when PassArgs::nt is set
     PassLauncher launch_nt = nullptr;
-    PassLauncher pick(const PassArgs &a) const { return (a.nt && launch_nt) ? launch_nt : launch; }
+    // the same pass with wide tiles (strided complex128 passes past 512 points)
+    PassLauncher launch_wide = nullptr, launch_wide_nt = nullptr;
+    int n_wide = 0, pencils_wide = 0;   // length, pencils per wide tile
+    PassLauncher pick(const PassArgs &a) const
+    {
+        if (launch_wide && wide_pays(n_wide, pencils_wide, a.npencils, a.inner, a.nt != 0))
+            return a.nt ? launch_wide_nt : launch_wide;
+        return (a.nt && launch_nt) ? launch_nt : launch;
+    }
 };
 
 // esize: 16 (complex128) or 8 (complex64); mx asks for the matrix-core

@@ -71,9 +71,10 @@ __device__ __forceinline__ int64_t pencil_obase(const PassArgs &a, uint32_t loca
     return (int64_t)q * a.oouter + (int64_t)(local - q * in) * a.oistep;
 }
 
-template <typename V, int N, bool CONTIG, bool MX = false, bool NT = false, bool MULTI = false> struct PassCfg {
+template <typename V, int N, bool CONTIG, bool MX = false, bool MULTI = false, bool WIDE = false> struct PassCfg {
+    static_assert(!WIDE || (std::is_same<V, double2>::value && has_wide(N, CONTIG)), "no wide tiles for this pass");
     // complex128 tiles exchange real and imaginary parts in two rounds
-    static constexpr bool SPLIT = std::is_same<V, double2>::value && split_exchange(N, CONTIG, NT);
+    static constexpr bool SPLIT = std::is_same<V, double2>::value && (WIDE || split_exchange(N));
     using LdsT = typename std::conditional<SPLIT, double, V>::type;   // LDS element
     static constexpr RadixPlan RP = radix_plan(N);
     // a multi-output pass holds its elements twice: in groups of more than 18
@@ -90,7 +91,7 @@ template <typename V, int N, bool CONTIG, bool MX = false, bool NT = false, bool
     // points 299 -> 270 us, 576: 167 -> 146); not where part-filled rounds of
     // radix-3 butterflies would spill (768 points 210 -> 242)
     static constexpr int MIN_WAVES =
-        SPLIT && wide_strided(N, CONTIG, NT) && (GP.elems <= 16 || (N % 9 == 0 && GP.elems <= 18)) ? 4 : 1;
+        WIDE && (GP.elems <= 16 || (N % 9 == 0 && GP.elems <= 18)) ? 4 : 1;
     static constexpr int M = GP.elems;
     static constexpr int LS = lds_pencil_stride(N);
     // whether a contiguous tile moves as one block (block_to_rows), with
@@ -589,10 +590,11 @@ __device__ __forceinline__ void rows_to_block(const V (&v)[M], V (&lin)[Cfg::LIN
 // the extra threads only take part in the barriers.  OWN: the tile of a pass
 // kernel of its own, whose workgroup is the tile's THREADS; only there may it
 // move as one block (PassCfg::block), generate its input or evolve it.
-template <typename V, int N, bool CONTIG, bool MX, bool MULTI = false, bool NT = false, bool OWN = false>
+template <typename V, int N, bool CONTIG, bool MX, bool MULTI = false, bool NT = false, bool OWN = false,
+          bool WIDE = false>
 __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int tid, V *lds, real_t<V> *gtab)
 {
-    using Cfg = PassCfg<V, N, CONTIG, MX, NT, MULTI>;
+    using Cfg = PassCfg<V, N, CONTIG, MX, MULTI, WIDE>;
     using R = real_t<V>;
     constexpr RadixPlan RP = Cfg::RP;
     constexpr GroupPlan GP = Cfg::GP;
@@ -1081,9 +1083,9 @@ template <bool REMAP> __device__ __forceinline__ int64_t tile_of_block(int64_t b
 #ifndef FB_XCD_REMAP_NARROW
 #define FB_XCD_REMAP_NARROW 1
 #endif
-template <typename V, int N, bool CONTIG, bool MX, bool NT> constexpr bool xcd_remap()
+template <typename V, int N, bool CONTIG, bool MX, bool WIDE = false> constexpr bool xcd_remap()
 {
-    constexpr int seg_bytes = PassCfg<V, N, CONTIG, MX, NT>::P * (int)sizeof(V);
+    constexpr int seg_bytes = PassCfg<V, N, CONTIG, MX, false, WIDE>::P * (int)sizeof(V);
     return FB_XCD_REMAP || (FB_XCD_REMAP_MX_STRIDED && MX && !CONTIG) ||
            (FB_XCD_REMAP_NARROW && !CONTIG && seg_bytes < 128);
 }
@@ -1091,28 +1093,29 @@ template <typename V, int N, bool CONTIG, bool MX, bool NT> constexpr bool xcd_r
 // True when the pass kind has a non-temporal instance (NT = true).
 template <typename V, bool CONTIG> constexpr bool has_nt() { return nt_load<V, CONTIG>() || nt_store<V, CONTIG>(); }
 
-template <typename V, int N, bool CONTIG, bool MX, bool NT = false>
-__global__ void __launch_bounds__((PassCfg<V, N, CONTIG, MX, NT>::THREADS), (PassCfg<V, N, CONTIG, MX, NT>::MIN_WAVES))
+template <typename V, int N, bool CONTIG, bool MX, bool NT = false, bool WIDE = false>
+__global__ void __launch_bounds__((PassCfg<V, N, CONTIG, MX, false, WIDE>::THREADS),
+                                  (PassCfg<V, N, CONTIG, MX, false, WIDE>::MIN_WAVES))
     FB_OCCUPANCY fft_pass(PassArgs a)
 {
-    using Cfg = PassCfg<V, N, CONTIG, MX, NT>;
+    using Cfg = PassCfg<V, N, CONTIG, MX, false, WIDE>;
     __shared__ typename Cfg::LdsT lds[Cfg::lds_elems(NT && nt_load<V, CONTIG>())];
     __shared__ real_t<V> gtab[CONTIG ? N : 1];
-    pass_tile<V, N, CONTIG, MX, false, NT, true>(a, tile_of_block<xcd_remap<V, N, CONTIG, MX, NT>()>(blockIdx.x, gridDim.x),
-                                           threadIdx.x, (V *)lds, gtab);
+    pass_tile<V, N, CONTIG, MX, false, NT, true, WIDE>(
+        a, tile_of_block<xcd_remap<V, N, CONTIG, MX, WIDE>()>(blockIdx.x, gridDim.x), threadIdx.x, (V *)lds, gtab);
 }
 
 // Contiguous evolve pass with several outputs: the tile's spectrum is read
 // once and output j (evolution constant ev_cs[j]) is written at
 // out + j out_step, for j < nout.
 template <typename V, int N, bool MX, bool NT = false>
-__global__ void __launch_bounds__((PassCfg<V, N, true, MX, NT, true>::THREADS)) FB_OCCUPANCY fft_pass_multi(PassArgs a)
+__global__ void __launch_bounds__((PassCfg<V, N, true, MX, true>::THREADS)) FB_OCCUPANCY fft_pass_multi(PassArgs a)
 {
-    using Cfg = PassCfg<V, N, true, MX, NT, true>;
+    using Cfg = PassCfg<V, N, true, MX, true>;
     __shared__ typename Cfg::LdsT lds[Cfg::lds_elems_multi()];
     __shared__ real_t<V> gtab[N];
-    pass_tile<V, N, true, MX, true, NT, true>(a, tile_of_block<xcd_remap<V, N, true, MX, NT>()>(blockIdx.x, gridDim.x),
-                                        threadIdx.x, (V *)lds, gtab);
+    pass_tile<V, N, true, MX, true, NT, true>(a, tile_of_block<xcd_remap<V, N, true, MX>()>(blockIdx.x, gridDim.x),
+                                              threadIdx.x, (V *)lds, gtab);
 }
 
 }  // namespace fb

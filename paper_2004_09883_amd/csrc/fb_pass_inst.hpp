@@ -8,15 +8,15 @@
 
 namespace fb {
 
-template <typename V, int N, bool CONTIG, bool MX, bool NT = false>
+template <typename V, int N, bool CONTIG, bool MX, bool NT = false, bool WIDE = false>
 hipError_t launch_pass(const PassArgs &a, hipStream_t st)
 {
-    using Cfg = PassCfg<V, N, CONTIG, MX, NT>;
+    using Cfg = PassCfg<V, N, CONTIG, MX, false, WIDE>;
     constexpr int64_t UNIT = std::is_same<V, c2x>::value ? 2 : 1;   // pencils per tile slot
     if (!pass_args_ok(a, CONTIG)) return hipErrorInvalidValue;
     const int64_t blocks = (a.npencils + UNIT * Cfg::P - 1) / (UNIT * Cfg::P);
     if (blocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL((fft_pass<V, N, CONTIG, MX, NT>), dim3((unsigned)blocks), dim3(Cfg::THREADS), 0, st, a);
+    hipLaunchKernelGGL((fft_pass<V, N, CONTIG, MX, NT, WIDE>), dim3((unsigned)blocks), dim3(Cfg::THREADS), 0, st, a);
     return hipGetLastError();
 }
 
@@ -37,7 +37,14 @@ template <typename V, int N, bool CONTIG> PassInfo pass_info_k(bool mx)
         if (mx)
             return {&launch_pass<V, N, CONTIG, true>, CfgM::P, CfgM::THREADS, 1, nt_launcher<V, N, CONTIG, true>()};
     }
-    return {&launch_pass<V, N, CONTIG, false>, Cfg::P, Cfg::THREADS, 0, nt_launcher<V, N, CONTIG, false>()};
+    PassInfo pi{&launch_pass<V, N, CONTIG, false>, Cfg::P, Cfg::THREADS, 0, nt_launcher<V, N, CONTIG, false>()};
+    if constexpr (std::is_same<V, double2>::value && has_wide(N, CONTIG)) {
+        pi.launch_wide = &launch_pass<V, N, CONTIG, false, false, true>;
+        pi.launch_wide_nt = &launch_pass<V, N, CONTIG, false, true, true>;
+        pi.n_wide = N;
+        pi.pencils_wide = PassCfg<V, N, CONTIG, false, false, true>::P;
+    }
+    return pi;
 }
 
 template <typename V, int N> PassInfo pass_info(bool contig, bool mx)
@@ -93,7 +100,7 @@ template <bool B3> PassInfo find_pass_pair_t(int n, bool mx)
 
 template <typename V, int N, bool MX, bool NT = false> hipError_t launch_pass_multi(const PassArgs &a, hipStream_t st)
 {
-    using Cfg = PassCfg<V, N, true, MX, NT, true>;
+    using Cfg = PassCfg<V, N, true, MX, true>;
     if (!pass_args_ok(a, true)) return hipErrorInvalidValue;
     const int64_t blocks = (a.npencils + Cfg::P - 1) / Cfg::P;
     if (blocks <= 0) return hipSuccess;
@@ -110,8 +117,8 @@ template <typename V, int N, bool MX> constexpr PassLauncher nt_launcher_multi()
 // exists and MX is asked for).
 template <typename V, int N> PassInfo pass_info_multi(bool mx)
 {
-    using Cfg = PassCfg<V, N, true, false, false, true>;
-    using CfgM = PassCfg<V, N, true, true, false, true>;
+    using Cfg = PassCfg<V, N, true, false, true>;
+    using CfgM = PassCfg<V, N, true, true, true>;
     if constexpr (mx_capable<V, N, true>()) {
         if (mx) return {&launch_pass_multi<V, N, true>, CfgM::P, CfgM::THREADS, 1, nt_launcher_multi<V, N, true>()};
     }

@@ -288,7 +288,7 @@ constexpr int grouped_pencils(int n, int threads, bool contig, int esize, bool s
     return 1;
 }
 
-// Pencils per workgroup of the long strided complex128 passes (wide_strided
+// Pencils per workgroup of the long strided complex128 passes (has_wide
 // below): 8, a whole 128-byte line per row, while the workgroup's LDS (one
 // real part per element) and threads allow it, then 4.  More than 512 threads
 // leave 128 registers each, enough for 18 elements per thread.
@@ -299,32 +299,62 @@ constexpr int wide_pencils(int n, int threads, int elems)
     return p;
 }
 
-// Long strided complex128 passes with tiles of whole 128-byte lines per row
-// (wide_pencils).  With the 72 KB of one-round tiles a row segment is 64 bytes
-// at 1024 points and 16 at 4096, and the lines that neighbouring tiles share
-// have left the L2 before their turn.  A two-round exchange halves the tile's
-// LDS, and one tile may take most of a CU's.  Measured on grids above 192 MiB
-// (narrow -> wide, us): 576 points 180 -> 146, 768: 262 -> 210, 1024: 361 ->
-// 270, 1458: 478 -> 194, 2048: 723 -> 306, 4096: 1300 -> 455.  Grids that the
-// last-level cache holds gain from 2048 points on, and from 1152 where a thread
-// holds few elements (64 MiB: 1458 25.3 -> 23.5, 2048 35 -> 31, 2304 28.2 ->
-// 22.5, 4096 43.8 -> 40.6, but 1024 26.1 -> 39.4, 1536 27.6 -> 29.3, 1944 31.8 ->
-// 34.3); the others are wide in their non-temporal instance (nt) alone.
-constexpr bool wide_strided(int n, bool contig, bool nt)
+// Long strided complex128 passes have a second instance, with tiles of whole
+// 128-byte lines per row (wide_pencils).  With the 72 KB of one-round tiles a
+// row segment is 64 bytes at 1024 points and 16 at 4096, and the lines that
+// neighbouring tiles share have left the L2 before their turn.  A two-round
+// exchange halves the tile's LDS, and one tile may take most of a CU's.
+constexpr bool has_wide(int n, bool contig) { return FB_SPLIT_EXCHANGE && !contig && n > 512; }
+
+// Whether a pass of `npencils` pencils takes its wide instance (`pencils` per
+// tile); `inner` pencils lie side by side, rows `inner` elements apart or more;
+// nt: non-temporal accesses.  The wide tiles are fewer and larger: they need
+// enough of them for the 256 CUs, and whole lines (rows that start inside a
+// line make two of every segment, and the caches join narrow segments well).
+//
+// Measured (wide / narrow time; 22 lengths, 16 to 65536 pencils, x and y passes,
+// grids in the caches and out of them):
+//  - fewer than 128 tiles: 1.0 to 2.5 everywhere;
+//  - up to 1024 points, where narrow rows are 64 bytes: 0.9 to 1.8 with cached
+//    accesses and 1.0 to 1.6 with rows inside lines.  Non-temporal 0.67 to 0.94
+//    for 648 and 729 points from 160 tiles on, 0.70 to 0.98 for 972 and 1024 from
+//    360; 576, 768 and 864 points 0.86 to 1.10 from 480, above the last-level
+//    cache 1.04 to 1.17, and 0.80 to 1.05 from 288 MiB on with rows 64 KB apart;
+//  - past 1024 points, whole lines: non-temporal 0.35 to 0.97 from 160 tiles on
+//    (128 for 2187 and 2916 points, 0.81 to 0.88).  Cached, 1536, 1728 and 2048
+//    points 0.41 to 0.99 from 128 MiB on, 0.89 to 1.01 where the tiles are one
+//    per CU (2048 x 2048: 35 -> 31 us), else 0.9 to 1.4; the others 0.28 to 1.0,
+//    but 1.0 to 1.4 between 300 and 800 tiles while the caches hold the grid
+//    (1152 x 3072: 27.6 / 32.9 us there and 32 / 25 us from memory at 2048);
+//  - rows inside lines: 0.77 to 0.91 for 1152, 1296, 1458, 2048 and 3072 points
+//    from 192 MiB on (1.1 to 1.6 below), 0.9 to 1.4 for 1536 and 1728 points at
+//    any size, for the others 0.45 to 0.95, with a few of up to 1.27 around 300
+//    and 550 tiles; rows of fewer than 9 (1152 .. 3072) or 4 pencils 1.1 to 1.4.
+constexpr bool wide_pays(int n, int pencils, int64_t npencils, int64_t inner, bool nt)
 {
-    if (!FB_SPLIT_EXCHANGE || contig) return false;
-    if (nt || n >= 2048) return n > 512;
-    return n > 1024 && grouped(n, contig, false) && group_plan(n, true).elems <= 18;
+    constexpr int64_t MiB = 1 << 20;
+    const int64_t tiles = (npencils + pencils - 1) / pencils, bytes = npencils * n * 16;
+    const bool whole = inner % 8 == 0;
+    if (n <= 1024) {
+        if (!whole || !nt) return false;
+        if (n % 96 == 0) return tiles >= 480 && (bytes < 192 * MiB || (bytes >= 288 * MiB && inner >= 4096));
+        return tiles >= (n < 900 ? 160 : 360);
+    }
+    const int64_t least = n % 729 == 0 ? 128 : 160;
+    if (whole) {
+        if (!nt && (n == 1536 || n == 1728 || n == 2048))
+            return bytes >= 128 * MiB || (tiles >= 224 && tiles <= 256);
+        return tiles >= least;
+    }
+    if (n < 1500 || n == 2048 || n == 3072) return bytes >= 192 * MiB && inner >= 9;
+    return n >= 1944 && tiles >= least && inner >= 4;
 }
 
 // Whether a complex128 pass exchanges real and imaginary parts in two rounds:
 // up to 256 points it lets more tiles share a CU (at 257 .. 512 points one
-// round was faster, the 512-point x pass 196 against 215 us), and the wide
-// strided passes need it.
-constexpr bool split_exchange(int n, bool contig, bool nt)
-{
-    return (FB_SPLIT_EXCHANGE && n <= FB_SPLIT_MAX_N) || wide_strided(n, contig, nt);
-}
+// round was faster, the 512-point x pass 196 against 215 us); the wide strided
+// tiles always do.
+constexpr bool split_exchange(int n) { return FB_SPLIT_EXCHANGE && n <= FB_SPLIT_MAX_N; }
 
 constexpr int pencils_per_wg(int n, bool contig, int esize, bool mx = false, bool split = false, bool groups = true)
 {

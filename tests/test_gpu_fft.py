@@ -178,6 +178,38 @@ def test_wide_strided_tiles_c128(shape):
         assert rel_l2(np.moveaxis(host(t), 2 - axis, 2), ref) < TOL[fb.FB_C128], direction
 
 
+# one grid per length past 512 whose x pass takes the wide tiles, the last
+# tile part-filled where the rule lets it be
+WIDE_X_GRIDS = [(576, 8, 4096), (648, 8, 2592), (729, 8, 2304), (768, 8, 3072), (864, 6, 4096), (972, 6, 2592),
+                (1024, 3, 4096), (1152, 3, 512), (1152, 27, 486), (1296, 1, 1296), (1296, 27, 486), (1458, 1, 1296),
+                (1536, 2, 972), (1728, 1, 1024), (1944, 1, 648), (1944, 3, 243), (2048, 1, 2048), (2048, 81, 81),
+                (2187, 1, 512), (2187, 9, 81), (2304, 1, 729), (2592, 1, 729), (2916, 1, 729), (3072, 1, 768),
+                (3072, 27, 162), (3456, 1, 729), (3888, 1, 729), (4096, 1, 729), (4096, 1, 648)]
+
+
+@pytest.mark.parametrize("shape", WIDE_X_GRIDS)
+def test_wide_and_narrow_tiles_give_the_same_bits(shape):
+    """The x pass of a grid in wide tiles against the same pencils, 64 of the
+    first and the last 27, as grids of their own whose tiles are narrow."""
+    print(f"wide and narrow shape={shape}", flush=True)
+    n, m = shape[0], shape[1] * shape[2]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    x = torch.view_as_complex(torch.randn(shape + (2,), dtype=torch.float64, device="cuda", generator=g))
+    plan = fb.Plan(*shape, fb.FB_C128)
+    y = torch.empty_like(x)
+    for direction in (fb.FB_FORWARD, fb.FB_INVERSE):
+        fb.fb_fft3d_exec_axes(plan, x, y, direction, 4)
+        for cols in (slice(0, 64), slice(m - 27, m)):
+            part = x.view(n, m)[:, cols].contiguous().view(n, 1, -1)
+            small = fb.Plan(n, 1, part.shape[2], fb.FB_C128)
+            fb.fb_fft3d_exec_axes(small, part, part, direction, 4)
+            assert torch.equal(part.view(n, -1), y.view(n, m)[:, cols]), (direction, cols)
+    t = x.clone()
+    fb.fb_fft3d_exec_axes(plan, t, t, fb.FB_INVERSE, 4)
+    assert torch.equal(t, y)
+
+
 def test_round_trip_c128():
     shape = (64, 32, 96)
     x = inputs.uniform_grid(shape, 5)
