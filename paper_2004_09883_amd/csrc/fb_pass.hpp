@@ -94,14 +94,18 @@ template <typename V, int N, bool CONTIG, bool MX = false, bool MULTI = false, b
         WIDE && (GP.elems <= 16 || (N % 9 == 0 && GP.elems <= 18)) ? 4 : 1;
     static constexpr int M = GP.elems;
     static constexpr int LS = lds_pencil_stride(N);
-    // whether a contiguous tile moves as one block (block_to_rows), with
-    // cached accesses and with non-temporal ones
-    static constexpr bool block(bool nt)
+    // the grid, in tiles, from which a contiguous pass moves its tiles as one
+    // block each (block_to_rows), with cached accesses and with non-temporal
+    // ones; 0: never
+    static constexpr int block_tiles(bool nt)
     {
         constexpr int seg = T * (int)sizeof(V);   // bytes of a pencil that its threads access together
-        if (!CONTIG || MX) return false;
-        return nt ? N < 512 && seg % 128 != 0 && (seg < 128 || N % 9 == 0 || !SPLIT) : N <= 48;
+        constexpr int waves = (THREADS + 63) / 64;
+        if (!CONTIG || MX) return 0;
+        if (nt && !(N < 512 && seg % 128 != 0 && (seg < 128 || N % 9 == 0 || !SPLIT))) return 0;
+        return (block_waves(N, (int)sizeof(V), GP.count == 1, nt, MULTI) + waves - 1) / waves;
     }
+    static constexpr bool block(bool nt) { return block_tiles(nt) > 0; }
     // LDS elements of a pass kernel's tile.  Non-temporal contiguous tiles of
     // up to 256 complex128 points ask for 20 KB per wavefront, which keeps 8 of
     // them on a CU: with the 14 that their registers and rows allow, the grid
@@ -507,10 +511,10 @@ __device__ __forceinline__ void store_tile_contiguous(const PassArgs &a, int64_t
 // 90, 432: 96 -> 84.  Longer passes hold one or two pencils per tile and lose
 // (729 complex128 163 -> 227, 1944 complex64 121 -> 135), and so does a
 // two-round exchange whose accesses pass a line anyway (192 complex128 148 ->
-// 153).  Cached, 64 and 32 MiB: complex128 16 points 33 -> 21, 27: 37 -> 28,
-// 48: 21 -> 21; complex64 16: 31 -> 12, 24: 25 -> 12, 48: 15 -> 12; from 64
-// points on the caches join the accesses and the round trips cost (complex128
-// 64: 19.6 -> 22.1, complex64 96: 13.0 -> 14.2).
+// 153).  Cached, 64 and 32 MiB: complex128 16 points 33 -> 21, 27: 37 -> 28;
+// complex64 16: 31 -> 12, 24: 25 -> 12, 48: 15 -> 12; from 64 points on the
+// caches join the accesses and the round trips cost (complex128 64: 19.6 ->
+// 22.1, complex64 96: 13.0 -> 14.2).  Grid sizes: block_waves.
 template <typename Cfg, int N, typename V, typename LdsT, int M>
 __device__ __forceinline__ void block_to_rows(const V (&lin)[Cfg::LIN], V (&v)[M], int tid, int t, LdsT *lds, LdsT *row)
 {
@@ -675,12 +679,12 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
             }
         }
     };
-    // the tile moves as one block (uniform): pencils back to back, and enough
-    // tiles for the device's 256 CUs; with fewer the pass is one latency after
-    // another and the LDS round trips add theirs (48 x 12 x 27 complex64: the z
-    // pass 8.5 us as blocks, 5.9 pencil-wise)
-    constexpr bool STAGE = OWN && Cfg::block(NT && nt_load<V, CONTIG>());
-    [[maybe_unused]] const bool block = STAGE && !a.seg_off && a.outer == N && gridDim.x >= 256;
+    // the tile moves as one block (uniform): pencils back to back, in a grid
+    // large enough (block_waves)
+    constexpr bool NT_TILE = NT && nt_load<V, CONTIG>();
+    constexpr bool STAGE = OWN && Cfg::block(NT_TILE);
+    [[maybe_unused]] const bool block =
+        STAGE && !a.seg_off && a.outer == N && gridDim.x >= (unsigned)Cfg::block_tiles(NT_TILE);
     [[maybe_unused]] const int64_t block0 = tile * P * N;   // its first element, and its length
     [[maybe_unused]] const int block_n = (int)(a.npencils - tile * P < P ? a.npencils - tile * P : P) * N;
     using LdsT = typename Cfg::LdsT;

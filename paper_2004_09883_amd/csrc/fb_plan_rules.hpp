@@ -288,6 +288,51 @@ constexpr int grouped_pencils(int n, int threads, bool contig, int esize, bool s
     return 1;
 }
 
+// Wavefronts of a contiguous pass from which its tiles move as one block
+// (block_to_rows in fb_pass.hpp) instead of pencil by pencil; 0: never.  A pass
+// with few wavefronts per CU is one latency after another, and the LDS round
+// trips of a block add theirs; with more of them the accesses count, and they
+// count most where they are non-temporal.  one_group: all stages in registers.
+//
+// Measured (block / pencil-wise time; 1 to 500 MiB; repeated on the same grid /
+// on grids that come from memory):
+//  - non-temporal complex128: 6 to 36 points 0.9 to 1.5 / 0.5 to 1.0 at 256
+//    wavefronts (24 and 32 points 1.1 to 1.5 / 1.05), 0.3 to 0.9 / 0.2 to 0.7 at
+//    1024; 48 to 72: 0.85 to 1.06 / 0.73 to 1.0 at 1024; up to 243 points 1.0 to
+//    1.5 below 2048, 0.5 to 0.95 from there; 288, 324: 1.05 at 5462, 0.9 from
+//    8192; 432, 486: 1.0 at 8192, 0.93 to 0.99 from 16384.  2 points 1.1 at 2048,
+//    0.8 at 4096; 3: 0.85 at 2048; 4: 1.0 / 0.9 at 1024;
+//  - non-temporal complex64: 6 to 16 points 0.7 to 1.2 / 0.4 to 1.0 at 1024; 18 to
+//    48: 0.5 to 1.3 / 0.4 to 0.7 at 512, 54 to 72 and 96: 0.7 to 1.0 at 768; up to
+//    243 points 1.2 to 1.5 at 600, 0.8 to 1.1 at 1536, 0.6 to 0.9 from 2300 on;
+//    288 to 486: 1.0 to 1.4 at 2048, 0.85 to 1.1 from 4096.  2 points 1.1 to 1.2 at
+//    any size, 3: 1.0, 4: 0.8 to 1.0 from 4096;
+//  - cached complex128: 8 to 27 points in one group 1.0 to 1.5 at 512, 0.6 to 0.9
+//    from 1024; 24 and 36: 1.1 to 1.2 at 1024, 0.8 to 0.98 from 2048; 3: 1.1 at
+//    2048, 0.9 at 4096; 2, 32 and 48: 1.0 to 1.4 at any size;
+//  - cached complex64: 0.65 to 0.96 from 2048 on (9 and 36 points 1.1 to 1.4 at
+//    512; 18: 1.1 to 1.2 at 2048, 1.0 and 0.93 at 4096); 2, 3, 4 and 27: 1.0 to
+//    1.8 at any size;
+//  - cached passes with several outputs, which store more than they load: 5 steps
+//    as a whole 0.92 to 1.0 from 512 (complex128, up to 18 points; longer ones 1.0
+//    to 1.08) and 1024 (complex64, 0.93 to 1.0).
+constexpr int block_waves(int n, int esize, bool one_group, bool nt, bool multi)
+{
+    if (esize == 16) {
+        if (nt && n <= 4) return n == 2 ? 4096 : n == 3 ? 2048 : 1024;
+        if (nt && n <= 36) return n == 24 || n == 32 ? 512 : 256;
+        if (nt) return n <= 72 ? 1024 : n <= 243 ? 2048 : n < 400 ? 8192 : 16384;
+        if (multi) return n == 2 || n > 18 ? 0 : 512;
+        if (n > 36 || n == 2 || n == 32) return 0;
+        return n == 3 ? 4096 : n == 4 ? 2048 : one_group || n <= 16 ? 1024 : 2048;
+    }
+    if (nt && n <= 48) return n <= 3 ? 0 : n == 4 ? 4096 : n <= 16 ? 1024 : multi && n == 27 ? 256 : 512;
+    if (nt) return n <= 72 || n == 96 ? 768 : n <= 243 ? 1536 : 4096;
+    if (n <= 4 || n > 48) return 0;
+    if (multi) return 1024;
+    return n == 27 ? 0 : n == 18 ? 4096 : 2048;
+}
+
 // Pencils per workgroup of the long strided complex128 passes (has_wide
 // below): 8, a whole 128-byte line per row, while the workgroup's LDS (one
 // real part per element) and threads allow it, then 4.  More than 512 threads

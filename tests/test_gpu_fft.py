@@ -210,6 +210,49 @@ def test_wide_and_narrow_tiles_give_the_same_bits(shape):
     assert torch.equal(t, y)
 
 
+# grids whose z pass moves its tiles as one block, the last tile part-filled;
+# the last two are above the last-level cache (non-temporal accesses)
+BLOCK_Z_GRIDS = [((243, 288, 27), fb.FB_C128), ((243, 288, 16), fb.FB_C128), ((243, 324, 36), fb.FB_C128),
+                 ((486, 288, 16), fb.FB_C64), ((243, 324, 36), fb.FB_C64), ((243, 216, 48), fb.FB_C64),
+                 ((243, 324, 36), fb.FB_C64_SPLITBF16), ((243, 243, 216), fb.FB_C128), ((486, 324, 162), fb.FB_C64)]
+
+
+@pytest.mark.parametrize("shape,dtype", BLOCK_Z_GRIDS)
+def test_block_tiles_against_pencils_evolved_generated_and_with_several_outputs(shape, dtype):
+    """Tiles moved as one block give the bits of the same pencils in a grid
+    too small for it; with generated input those of a filled grid; with
+    several outputs those of single steps; evolved, the oracle's values; and
+    nothing past the last output grid is written."""
+    print(f"block tiles shape={shape} dtype={dtype}", flush=True)
+    n, tol = math.prod(shape), TOL[dtype]
+    plan = fb.Plan(*shape, dtype)
+    x = torch.empty(shape, dtype=plan.torch_dtype, device="cuda")
+    fb.fb_fill_uniform(plan, x, 31)
+    y = torch.empty_like(x)
+    plane = fb.Plan(1, *shape[1:], dtype)
+    for direction in (fb.FB_FORWARD, fb.FB_INVERSE):
+        fb.fb_fft3d_exec_axes(plan, x, y, direction, 1)
+        for i in (0, shape[0] - 1):
+            part = x[i:i + 1].clone()
+            fb.fb_fft3d_exec_axes(plane, part, part, direction, 1)
+            assert torch.equal(part, y[i:i + 1]), (direction, i)
+    fb.fb_fft3d_exec(plan, x, x, fb.FB_FORWARD)
+    fb.fb_fft3d_forward_uniform(plan, 31, y)
+    assert torch.equal(x, y)
+    ts = [1.0, 2.0, 3.0]
+    buf = torch.full((3 * n + 64,), 7.0, dtype=plan.torch_dtype, device="cuda")
+    multi = buf[:3 * n].view((3,) + shape)
+    fb.fb_spectral_steps(plan, x, multi, 1e-5, ts)
+    assert torch.all(buf[3 * n:] == 7.0)
+    for j, t in enumerate(ts):
+        fb.fb_spectral_step(plan, x, y, 1e-5, t)
+        assert torch.equal(y, multi[j]), j
+    if n < 1 << 23:
+        X = oracle.fft3d(as_seen(inputs.uniform_grid(shape, 31), dtype), -1)
+        assert rel_l2(host(x), X) < tol
+        assert rel_l2(host(y), oracle.fft3d(oracle.evolve(X, 1e-5, ts[-1]), +1)) < tol
+
+
 def test_round_trip_c128():
     shape = (64, 32, 96)
     x = inputs.uniform_grid(shape, 5)

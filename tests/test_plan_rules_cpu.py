@@ -5,12 +5,13 @@ import subprocess
 
 import pytest
 
-from test_gpu_fft import WIDE_X_GRIDS
+from paper_2004_09883_amd import fb
+from test_gpu_fft import BLOCK_Z_GRIDS, WIDE_X_GRIDS
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2004_09883_amd", "csrc")
 LONG = [576, 648, 729, 768, 864, 972, 1024, 1152, 1296, 1458, 1536, 1728, 1944, 2048, 2187, 2304, 2592, 2916, 3072,
         3456, 3888, 4096]
-PROGRAM = r"""
+WIDE_PROGRAM = r"""
 #include <cstdio>
 #include "fb_plan_rules.hpp"
 int main()
@@ -26,11 +27,29 @@ int main()
 """
 
 
-@pytest.fixture(scope="module")
-def wide(tmp_path_factory):
-    """(n, pencils, inner, nt) rows -> (pencils per wide tile, wide or not)"""
-    d = tmp_path_factory.mktemp("rules")
-    (d / "rules.cpp").write_text(PROGRAM)
+# tiles of a contiguous pass and the wavefronts from which it moves them as blocks
+BLOCK_PROGRAM = r"""
+#include <cstdio>
+#include "fb_plan_rules.hpp"
+int main()
+{
+    using namespace fb;
+    long n, np, es;
+    int nt;
+    while (scanf("%ld %ld %ld %d", &n, &np, &es, &nt) == 4) {
+        const bool split = es == 16 && split_exchange((int)n), g = grouped((int)n, true, false);
+        const GroupPlan gp = group_plan((int)n, g);
+        const int p = pencils_per_wg((int)n, true, (int)es, false, split, g);
+        const long tiles = (np + p - 1) / p, waves = tiles * ((p * gp.threads + 63) / 64);
+        printf("%ld %ld %d\n", tiles, waves, block_waves((int)n, (int)es, gp.count == 1, nt != 0, false));
+    }
+}
+"""
+
+
+def compiled(d, program):
+    """ask(rows of four integers) -> one tuple of integers per row"""
+    (d / "rules.cpp").write_text(program)
     subprocess.run(["g++", "-std=c++17", "-I", CSRC, str(d / "rules.cpp"), "-o", str(d / "rules")], check=True)
 
     def ask(rows):
@@ -38,6 +57,18 @@ def wide(tmp_path_factory):
                            text=True, check=True)
         return [tuple(map(int, line.split())) for line in r.stdout.split("\n") if line]
     return ask
+
+
+@pytest.fixture(scope="module")
+def wide(tmp_path_factory):
+    """(n, pencils, inner, nt) -> (pencils per wide tile, wide or not)"""
+    return compiled(tmp_path_factory.mktemp("wide"), WIDE_PROGRAM)
+
+
+@pytest.fixture(scope="module")
+def block(tmp_path_factory):
+    """(n, pencils, element bytes, nt) -> (tiles, wavefronts, least wavefronts for blocks or 0)"""
+    return compiled(tmp_path_factory.mktemp("block"), BLOCK_PROGRAM)
 
 
 def test_wide_tiles_need_enough_tiles_for_the_device(wide):
@@ -64,3 +95,22 @@ def test_grids_of_the_gpu_test_are_wide(wide):
         assert is_wide, row
     assert {r[0] for r in rows} == set(LONG)
     assert not any(w for _, w in wide([(n, 91, 91, 0) for n in LONG]))
+
+
+def test_blocks_need_several_wavefronts_per_cu(block):
+    """No length moves blocks with fewer wavefronts than one per CU, or, with
+    cached accesses, four."""
+    for nt, floor in ((0, 1024), (1, 256)):
+        rows = [(n, 1, es, nt) for n in range(2, 512) for es in (8, 16)
+                if n in (2 ** a * 3 ** b for a in range(10) for b in range(6))]
+        assert all(least == 0 or least >= floor for _, _, least in block(rows))
+
+
+def test_grids_of_the_gpu_test_move_as_blocks(block):
+    """... and one plane of each does not."""
+    for planes, want in ((None, True), (1, False)):
+        rows = [(z, (planes or x) * y, 16 if dt == fb.FB_C128 else 8,
+                 int((planes or x) * y * z * (16 if dt == fb.FB_C128 else 8) >= 192 << 20))
+                for (x, y, z), dt in BLOCK_Z_GRIDS]
+        for row, (_, waves, least) in zip(rows, block(rows)):
+            assert (least > 0 and waves >= least) == want, (row, waves, least)
