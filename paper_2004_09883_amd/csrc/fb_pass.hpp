@@ -92,6 +92,11 @@ template <typename V, int N, bool CONTIG, bool MX = false, bool MULTI = false, b
     // radix-3 butterflies would spill (768 points 210 -> 242)
     static constexpr int MIN_WAVES =
         WIDE && (GP.elems <= 16 || (N % 9 == 0 && GP.elems <= 18)) ? 4 : 1;
+    // waves per SIMD that a multi-output pass is compiled for at most.  With the
+    // registers of three, the complex64 stages of 3 2^a points load their
+    // twiddles one after another, each waited for (5 steps of 64 x 64 x 48: the z
+    // pass 24.1 us, 20.6 with all in flight)
+    static constexpr int MAX_WAVES_MULTI = sizeof(V) == 8 && !MX && !GROUPED && N % 3 == 0 ? 2 : 8;
     static constexpr int M = GP.elems;
     static constexpr int LS = lds_pencil_stride(N);
     // the grid, in tiles, from which a contiguous pass moves its tiles as one
@@ -1113,7 +1118,8 @@ __global__ void __launch_bounds__((PassCfg<V, N, CONTIG, MX, false, WIDE>::THREA
 // once and output j (evolution constant ev_cs[j]) is written at
 // out + j out_step, for j < nout.
 template <typename V, int N, bool MX, bool NT = false>
-__global__ void __launch_bounds__((PassCfg<V, N, true, MX, true>::THREADS)) FB_OCCUPANCY fft_pass_multi(PassArgs a)
+__global__ void __launch_bounds__((PassCfg<V, N, true, MX, true>::THREADS))
+    __attribute__((amdgpu_waves_per_eu(1, (PassCfg<V, N, true, MX, true>::MAX_WAVES_MULTI)))) fft_pass_multi(PassArgs a)
 {
     using Cfg = PassCfg<V, N, true, MX, true>;
     __shared__ typename Cfg::LdsT lds[Cfg::lds_elems_multi()];
