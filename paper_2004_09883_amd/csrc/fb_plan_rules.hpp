@@ -308,10 +308,10 @@ constexpr int grouped_pencils(int n, int threads, bool contig, int esize, bool s
 //    288 to 486: 1.0 to 1.4 at 2048, 0.85 to 1.1 from 4096.  2 points 1.1 to 1.2 at
 //    any size, 3: 1.0, 4: 0.8 to 1.0 from 4096;
 //  - cached complex128: 8 to 27 points in one group 1.0 to 1.5 at 512, 0.6 to 0.9
-//    from 1024; 24 and 36: 1.1 to 1.2 at 1024, 0.8 to 0.98 from 2048; 3: 1.1 at
+//    from 1024 (16 points 0.92 and 0.99 at 512); 24 and 36: 1.1 to 1.2 at 1024, 0.8 to 0.98 from 2048; 3: 1.1 at
 //    2048, 0.9 at 4096; 2, 32 and 48: 1.0 to 1.4 at any size;
 //  - cached complex64: 0.65 to 0.96 from 2048 on (9 and 36 points 1.1 to 1.4 at
-//    512; 18: 1.1 to 1.2 at 2048, 1.0 and 0.93 at 4096); 2, 3, 4 and 27: 1.0 to
+//    512, 16 and 32 points 0.9 to 1.0 at 1024; 18: 1.1 to 1.2 at 2048, 1.0 and 0.93 at 4096); 2, 3, 4 and 27: 1.0 to
 //    1.8 at any size;
 //  - cached passes with several outputs, which store more than they load: 5 steps
 //    as a whole 0.92 to 1.0 from 512 (complex128, up to 18 points; longer ones 1.0
@@ -324,13 +324,13 @@ constexpr int block_waves(int n, int esize, bool one_group, bool nt, bool multi)
         if (nt) return n <= 72 ? 1024 : n <= 243 ? 2048 : n < 400 ? 8192 : 16384;
         if (multi) return n == 2 || n > 18 ? 0 : 512;
         if (n > 36 || n == 2 || n == 32) return 0;
-        return n == 3 ? 4096 : n == 4 ? 2048 : one_group || n <= 16 ? 1024 : 2048;
+        return n == 3 ? 4096 : n == 4 ? 2048 : n == 16 ? 512 : one_group || n <= 16 ? 1024 : 2048;
     }
     if (nt && n <= 48) return n <= 3 ? 0 : n == 4 ? 4096 : n <= 16 ? 1024 : multi && n == 27 ? 256 : 512;
     if (nt) return n <= 72 || n == 96 ? 768 : n <= 243 ? 1536 : 4096;
     if (n <= 4 || n > 48) return 0;
     if (multi) return 1024;
-    return n == 27 ? 0 : n == 18 ? 4096 : 2048;
+    return n == 27 ? 0 : n == 18 ? 4096 : n == 16 || n == 32 ? 1024 : 2048;
 }
 
 // Pencils per workgroup of the long strided complex128 passes (has_wide

@@ -99,8 +99,8 @@ def test_grids_of_the_gpu_test_are_wide(wide):
 
 def test_blocks_need_several_wavefronts_per_cu(block):
     """No length moves blocks with fewer wavefronts than one per CU, or, with
-    cached accesses, four."""
-    for nt, floor in ((0, 1024), (1, 256)):
+    cached accesses, two."""
+    for nt, floor in ((0, 512), (1, 256)):
         rows = [(n, 1, es, nt) for n in range(2, 512) for es in (8, 16)
                 if n in (2 ** a * 3 ** b for a in range(10) for b in range(6))]
         assert all(least == 0 or least >= floor for _, _, least in block(rows))
