@@ -13,9 +13,12 @@ namespace fb {
 // one launch.  A two-pass transform is one workgroup's work there, so a batch
 // whose longest transform outweighs an even share waits for it; one launch per
 // phase spreads its tiles over the device.  Measured (one launch / per phase,
-// us): 4096 + 64 transforms, balance 1.01: 1108 / 1119; 3000 + 10, 1.08: 725 /
-// 736; 2048 + 64, 1.69: 695 / 656; 1024 + 30, 3.5: 578 / 329; 128 + 32, 15.9:
-// 450 / 56; 64, 48: 449 / 35.
+// us): up to 1.25 either may win by a few per cent (4096 + 64 transforms, balance
+// 1.05: 1048 / 1026; 4096, 1.01: 882 / 905; 3000 + 64 of 256^2, 1.10: 690 / 705;
+// 4096 + 10, 1.19: 921 / 929; 1024 of 8192 points, 1.00: 83 / 92; 4096 of 4096
+// points, 1.00: 72 / 68), above it the phases: 3000 + 64, 1.36: 809 / 801; 2048 +
+// 64, 1.81: 673 / 611; 1024 + 64, 2.9: 596 / 381; 256, 13: 450 / 68; 64 + 64
+// of 256^2, 16: 449 / 54.
 #define FB_BATCH_MAX_BALANCE 1.25
 
 // One (length, pass) group of a batch.  The data pointers of `args` are

@@ -152,3 +152,42 @@ def test_unbalanced_batch_equals_per_group_bitwise(lens, n2d, side):
     i = len(lens) - 1
     o = batch.offsets[i]
     assert rel_l2(a[o:o + lens[i]].astype(np.complex128), ref_transform(batch, x, i, fb.FB_INVERSE)) < TOL
+
+
+@pytest.mark.parametrize("lens,n2d,side", [([6144] * 2048 + [256] * 8191, 0, 0), ([8192] * 1024 + [48] * 3000, 512, 64),
+                                           ([4096] * 2045, 0, 0)])
+def test_balanced_batch_in_one_launch_equals_per_group_bitwise(lens, n2d, side):
+    """Batches that mode 1 runs in one launch (their description's balance is
+    at most 1.25): the bits of the per-group mode, in and out of place, both
+    directions, and again on the same plan; 6144 points are split so that an
+    item holds two transforms."""
+    batch = fb.Batch(lens, n2d=n2d, side2d=side)
+    print("balanced batch:", batch.description, flush=True)
+    assert "onelaunch=1" in batch.description
+    assert float(batch.description.split("balance=")[1].split()[0]) <= 1.25, batch.description
+    x = packed_input(batch, 17)
+    for in_place in (False, True):
+        for direction in (fb.FB_FORWARD, fb.FB_INVERSE):
+            a = run(batch, x, direction, 0, in_place)
+            for _ in range(2):
+                assert np.array_equal(a, run(batch, x, direction, 1, in_place)), (in_place, direction)
+    for i in (0, 1, len(lens) // 2, len(lens) - 1, len(lens) + n2d - 1):
+        o = batch.offsets[i]
+        n = lens[i] if i < len(lens) else side * side
+        assert rel_l2(a[o:o + n].astype(np.complex128), ref_transform(batch, x, i, fb.FB_INVERSE)) < TOL, i
+
+
+def test_balanced_batch_is_one_launch():
+    """The launches that mode 1 makes, by the profile: one where the balance is
+    at most 1.25, one per phase above it."""
+    for lens, names in (([8192] * 1024, ["batch_onelaunch<c64>"]),
+                        ([8192] * 3, ["batch_persistent<c64,phase0>", "batch_persistent<c64,phase1>"])):
+        batch = fb.Batch(lens)
+        x = torch.zeros(batch.elements, dtype=torch.complex64, device="cuda")
+        y = torch.empty_like(x)
+        ws = torch.empty(256, dtype=torch.uint8, device="cuda")
+        fb.fb_profile_enable(True)
+        fb.fb_batch_exec(batch, x, y, ws, fb.FB_FORWARD, 1)
+        report = fb.fb_profile_report()
+        fb.fb_profile_enable(False)
+        assert [r["kernel"] for r in report] == names, batch.description
