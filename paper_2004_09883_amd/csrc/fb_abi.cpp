@@ -1150,30 +1150,36 @@ fb_batch *fb_batch_plan(const int64_t *lens, int n1d, int n2d, int64_t side2d, i
         }
         if (e != hipSuccess) break;
     }
-    fb::BatchGroup rows{}, cols{};
-    bool has2d = n2d > 0 && e == hipSuccess;
-    if (has2d) {
+    std::vector<fb::BatchGroup> rows2d, cols2d;   // one pair unless the images' rows pass FB_MAX_PENCILS
+    if (n2d > 0 && e == hipSuccess) {
         std::vector<int64_t> o2(b->off.begin() + n1d, b->off.end());
         int64_t *soff = dev_alloc<int64_t>(b, o2.size(), e);
         if (e == hipSuccess) e = hipMemcpy(soff, o2.data(), o2.size() * sizeof(int64_t), hipMemcpyHostToDevice);
-        const int64_t s = side2d;
-        rows = new_group(s, true);
-        set_geom(rows.args, n2d * s, s, soff, 1, s, 0, 1);
-        rows.in_sel = 0;
-        rows.out_sel = 1;
-        rows.tile_pencils = tile_pencils_of(fb::find_pass(esize, (int)s, true, false), nopass);
-        rows.ntiles = (n2d * s + rows.tile_pencils - 1) / rows.tile_pencils;
-        cols = new_group(s, false);
-        set_geom(cols.args, n2d * s, s, soff, s, 0, 1, s);
-        cols.in_sel = 1;
-        cols.out_sel = 1;
-        cols.last = 1;
-        cols.phase = 1;
-        cols.inv_scale = 1.0 / (double)(s * s);
-        cols.tile_pencils = tile_pencils_of(fb::find_pass_pair((int)s), nopass);
-        cols.ntiles = (n2d * s + cols.tile_pencils - 1) / cols.tile_pencils;
-        if (e == hipSuccess && (!group_in_bounds(rows, o2.back(), b->total) || !group_in_bounds(cols, o2.back(), b->total)))
-            e = hipErrorInvalidValue;
+        const int64_t s = side2d, per = fb::batch_images_per_group(s);
+        for (int64_t j0 = 0; e == hipSuccess && j0 < n2d; j0 += per) {
+            const int64_t cnt = n2d - j0 < per ? n2d - j0 : per;
+            fb::BatchGroup rows = new_group(s, true);
+            set_geom(rows.args, cnt * s, s, soff + j0, 1, s, 0, 1);
+            rows.in_sel = 0;
+            rows.out_sel = 1;
+            rows.tile_pencils = tile_pencils_of(fb::find_pass(esize, (int)s, true, false), nopass);
+            rows.ntiles = (cnt * s + rows.tile_pencils - 1) / rows.tile_pencils;
+            fb::BatchGroup cols = new_group(s, false);
+            set_geom(cols.args, cnt * s, s, soff + j0, s, 0, 1, s);
+            cols.in_sel = 1;
+            cols.out_sel = 1;
+            cols.last = 1;
+            cols.phase = 1;
+            cols.inv_scale = 1.0 / (double)(s * s);
+            cols.tile_pencils = tile_pencils_of(fb::find_pass_pair((int)s), nopass);
+            cols.ntiles = (cnt * s + cols.tile_pencils - 1) / cols.tile_pencils;
+            const int64_t last_off = o2[(size_t)(j0 + cnt - 1)];
+            if (e == hipSuccess &&
+                (!group_in_bounds(rows, last_off, b->total) || !group_in_bounds(cols, last_off, b->total)))
+                e = hipErrorInvalidValue;
+            rows2d.push_back(rows);
+            cols2d.push_back(cols);
+        }
     }
     if (e == hipSuccess && nopass) e = hipErrorInvalidValue;
     if (e != hipSuccess) {
@@ -1186,11 +1192,11 @@ fb_batch *fb_batch_plan(const int64_t *lens, int n1d, int n2d, int64_t side2d, i
     // phase 0: first passes, 2D rows, single-pass transforms; phase 1: second
     // passes and 2D columns (they read what phase 0 wrote)
     for (auto &g : pass1) b->groups.push_back(g);
-    if (has2d) b->groups.push_back(rows);
+    for (auto &g : rows2d) b->groups.push_back(g);
     for (auto &g : single) b->groups.push_back(g);
     b->phase1_begin = (int)b->groups.size();
     for (auto &g : pass2) b->groups.push_back(g);
-    if (has2d) b->groups.push_back(cols);
+    for (auto &g : cols2d) b->groups.push_back(g);
     if ((int)b->groups.size() > FB_BATCH_MAX_GROUPS) {
         fail(FB_ERR_UNSUPPORTED_SIZE, "too many distinct lengths in one batch (%d groups, at most %d)",
              (int)b->groups.size(), FB_BATCH_MAX_GROUPS);
@@ -1232,12 +1238,12 @@ fb_batch *fb_batch_plan(const int64_t *lens, int n1d, int n2d, int64_t side2d, i
     // the single-launch form: one grid sized for the largest tile kind of
     // either phase; item lists per workgroup
     {
-        const int np1 = (int)pass1.size();
+        const int np1 = (int)pass1.size(), np2d = (int)rows2d.size();
         std::vector<std::pair<int, int>> pairs;
         for (int i = 0; i < np1; i++) pairs.push_back({i, b->phase1_begin + i});
-        if (has2d) pairs.push_back({np1, b->phase1_begin + (int)pass2.size()});
+        for (int i = 0; i < np2d; i++) pairs.push_back({np1 + i, b->phase1_begin + (int)pass2.size() + i});
         std::vector<int> singles;
-        for (int i = np1 + (has2d ? 1 : 0); i < b->phase1_begin; i++) singles.push_back(i);
+        for (int i = np1 + np2d; i < b->phase1_begin; i++) singles.push_back(i);
         b->ol_lds_bytes = b->lds_bytes[0] > b->lds_bytes[1] ? b->lds_bytes[0] : b->lds_bytes[1];
         int per = 0;
         e = fb::batch_occupancy(b->ol_lds_bytes, &per, true);

@@ -70,7 +70,7 @@ struct PassArgs {
 // pencils `outer` apart and no output geometry of its own.
 inline bool pass_args_ok(const PassArgs &a, bool contig)
 {
-    if (a.npencils >= (int64_t(1) << 32) - (1 << 16) || a.inner < 1 || a.inner >= int64_t(1) << 32) return false;
+    if (a.npencils >= FB_MAX_PENCILS || a.inner < 1 || a.inner >= int64_t(1) << 32) return false;
     if (a.ostride && (a.oinner < 1 || a.oinner >= int64_t(1) << 32)) return false;
     if (a.evolve && (a.ev_d < 1 || a.ev_d >= int64_t(1) << 32)) return false;
     return !contig || (a.inner == 1 && a.stride == 1 && a.ostride == 0);

@@ -170,6 +170,14 @@ constexpr GroupPlan group_plan(int n, bool fuse)
     return best;
 }
 
+// Pencils that one pass can have: their numbers, a tile's overhang included,
+// fit 32 bits.  A batch of more images than that splits them over groups
+// (2^31 images of 2 x 2 are 64 GiB).
+#ifndef FB_MAX_PENCILS
+#define FB_MAX_PENCILS ((int64_t(1) << 32) - (1 << 16))
+#endif
+constexpr int64_t batch_images_per_group(int64_t side) { return (FB_MAX_PENCILS - 1) / side; }
+
 // LDS row of one pencil: one pad element every 16 (breaks the stride-R
 // pattern of the first exchange) and an odd total (consecutive pencils land
 // on different banks).

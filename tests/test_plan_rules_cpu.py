@@ -114,3 +114,23 @@ def test_grids_of_the_gpu_test_move_as_blocks(block):
                 for (x, y, z), dt in BLOCK_Z_GRIDS]
         for row, (_, waves, least) in zip(rows, block(rows)):
             assert (least > 0 and waves >= least) == want, (row, waves, least)
+
+
+def test_groups_of_images_keep_their_pencils_in_32_bits(tmp_path):
+    """Any number of images splits into groups whose pencils, a tile's
+    overhang included, are numbered in 32 bits."""
+    ask = compiled(tmp_path, r"""
+#include <cstdio>
+#include "fb_plan_rules.hpp"
+int main()
+{
+    long side, b, c, d;
+    while (scanf("%ld %ld %ld %ld", &side, &b, &c, &d) == 4)
+        printf("%ld %ld\n", (long)fb::batch_images_per_group(side), (long)FB_MAX_PENCILS);
+}
+""")
+    sides = [s for s in range(2, 4097) if s in {2 ** a * 3 ** b for a in range(13) for b in range(2)}]
+    for side, (per, limit) in zip(sides, ask([(s, 0, 0, 0) for s in sides])):
+        assert per >= 1 and per * side < limit <= 2 ** 32 - 2 ** 16
+        # the largest batch the plan takes, 2^31 - 1 images, in the fewest groups
+        assert -(-(2 ** 31 - 1) // per) <= -(-(2 ** 31 - 1) * side // (limit - 1)) + 1
