@@ -862,6 +862,13 @@ void set_geom(PassArgs &a, int64_t npencils, int64_t segp, const int64_t *seg_of
     a.stride = stride;
 }
 
+// The strided pass of a batch group: pencil pairs, single pencils where the
+// length is odd (as the tiles of the persistent kernels).
+PassInfo batch_strided_pass(int64_t n)
+{
+    return n % 2 == 0 ? fb::find_pass_pair((int)n) : fb::find_pass(8, (int)n, false, false);
+}
+
 int64_t gcd64(int64_t a, int64_t b) { return b == 0 ? a : gcd64(b, a % b); }
 
 // Pencils per tile of an instantiated pass; 1 (and `bad` set) when the
@@ -1112,7 +1119,7 @@ fb_batch *fb_batch_plan(const int64_t *lens, int n1d, int n2d, int64_t side2d, i
             g1.in_sel = 0;
             g1.out_sel = 2;   // fixed up per execution when out != in
             g1.last = 0;
-            const int P1 = tile_pencils_of(fb::find_pass_pair((int)n1), nopass);
+            const int P1 = tile_pencils_of(batch_strided_pass(n1), nopass);
             g1.ntiles = (cnt * n2 + P1 - 1) / P1;
             // a tile's outputs (pencils b .. b + P1 - 1 of one transform) form one
             // block of P1 n1 elements: write it whole when tiles do not straddle
@@ -1136,7 +1143,7 @@ fb_batch *fb_batch_plan(const int64_t *lens, int n1d, int n2d, int64_t side2d, i
             g2.out_sel = 1;
             g2.last = 1;
             g2.inv_scale = 1.0 / (double)L;
-            const int P2 = tile_pencils_of(fb::find_pass_pair((int)n2), nopass);
+            const int P2 = tile_pencils_of(batch_strided_pass(n2), nopass);
             g2.ntiles = (cnt * n1 + P2 - 1) / P2;
             g2.tile_pencils = P2;
             // the pass-2 kernel reads the pre-twiddle table at the element's offset
@@ -1171,7 +1178,7 @@ fb_batch *fb_batch_plan(const int64_t *lens, int n1d, int n2d, int64_t side2d, i
             cols.last = 1;
             cols.phase = 1;
             cols.inv_scale = 1.0 / (double)(s * s);
-            cols.tile_pencils = tile_pencils_of(fb::find_pass_pair((int)s), nopass);
+            cols.tile_pencils = tile_pencils_of(batch_strided_pass(s), nopass);
             cols.ntiles = (cnt * s + cols.tile_pencils - 1) / cols.tile_pencils;
             const int64_t last_off = o2[(size_t)(j0 + cnt - 1)];
             if (e == hipSuccess &&
@@ -1377,10 +1384,9 @@ fb_status fb_batch_exec(const fb_batch *b, const void *in, void *out, void *work
         a.inv = bufs.inv;
         a.nt = bufs.nt;
         a.scale = (bufs.inv && g.last) ? g.inv_scale : 1.0;
-        // contiguous groups move complex64 pencils, strided groups pencil pairs
-        const PassInfo pi = g.contig ? fb::find_pass(8, g.n, true, false) : fb::find_pass_pair(g.n);
+        const PassInfo pi = g.contig ? fb::find_pass(8, g.n, true, false) : batch_strided_pass(g.n);
         char name[96];
-        snprintf(name, sizeof name, "fft_pass<c64,n=%d,%s>", g.n, g.contig ? "contiguous" : "strided,pairs");
+        snprintf(name, sizeof name, "fft_pass<c64,n=%d,%s>", g.n, g.contig ? "contiguous" : g.n % 2 == 0 ? "strided,pairs" : "strided");
         const fb::PassLauncher launcher = pi.pick(a);
         e = timed_launch(name, 0.0, st, [&] { return launcher(a, st); });
         if (e != hipSuccess) return (fb_status)hip_fail(e, "batch pass launch");

@@ -29,15 +29,20 @@ namespace fb {
 constexpr int max_int(int a, int b) { return a > b ? a : b; }
 
 // Contiguous tiles hold complex64 pencils; strided tiles hold pencil pairs
-// (two adjacent pencils per 16-byte element).
+// (two adjacent pencils per 16-byte element), single pencils where the length
+// is odd: 3, the columns of 3 x 3 images, whose third column has no neighbour.
+template <int N> using strided_t = typename std::conditional<N % 2 == 0, c2x, float2>::type;
 template <int N> constexpr int kind_threads()
 {
-    return max_int(PassCfg<float2, N, true>::THREADS, PassCfg<c2x, N, false>::THREADS);
+    return max_int(PassCfg<float2, N, true>::THREADS, PassCfg<strided_t<N>, N, false>::THREADS);
+}
+template <typename V, int N, bool CONTIG> constexpr int tile_lds_bytes()
+{
+    return PassCfg<V, N, CONTIG>::P * PassCfg<V, N, CONTIG>::LS * (int)sizeof(V);
 }
 template <int N> constexpr int kind_lds_bytes()
 {
-    return max_int(PassCfg<float2, N, true>::P * PassCfg<float2, N, true>::LS * 8,
-                   PassCfg<c2x, N, false>::P * PassCfg<c2x, N, false>::LS * 16);
+    return max_int(tile_lds_bytes<float2, N, true>(), tile_lds_bytes<strided_t<N>, N, false>());
 }
 
 constexpr int batch_threads()
@@ -69,8 +74,7 @@ int batch_kind_lds_bytes(int n, bool contig)
     switch (n) {
 #define FB_KL(L)                                                                                          \
     case L:                                                                                                \
-        return contig ? PassCfg<float2, L, true>::P * PassCfg<float2, L, true>::LS * 8                   \
-                      : PassCfg<c2x, L, false>::P * PassCfg<c2x, L, false>::LS * 16;
+        return contig ? tile_lds_bytes<float2, L, true>() : tile_lds_bytes<strided_t<L>, L, false>();
         FB_BATCH_KINDS(FB_KL)
 #undef FB_KL
     default: return -1;
@@ -95,7 +99,7 @@ __device__ __forceinline__ void tile_fn(const BatchGroup *g, const BatchBuffers 
     a.nt = bufs.nt;
     a.scale = (bufs.inv && g->last) ? g->inv_scale : 1.0;
     if constexpr (CONTIG) pass_tile<float2, L, true, false>(a, tile, tid, (float2 *)lds, nullptr);
-    else pass_tile<c2x, L, false, false>(a, tile, tid, lds, nullptr);
+    else pass_tile<strided_t<L>, L, false, false>(a, tile, tid, (strided_t<L> *)lds, nullptr);
 }
 
 __device__ __forceinline__ void run_tile(const BatchGroup *g, const BatchBuffers &bufs, int64_t tile, int tid,

@@ -191,3 +191,29 @@ def test_balanced_batch_is_one_launch():
         report = fb.fb_profile_report()
         fb.fb_profile_enable(False)
         assert [r["kernel"] for r in report] == names, batch.description
+
+
+@pytest.mark.parametrize("lens,n2d", [([], 1), ([], 2), ([3], 5), ([48, 3, 256], 301), ([2] * 7, 4000), ([], 65536)])
+def test_images_of_odd_side(lens, n2d):
+    """3 x 3 images, whose columns do not pair up: every mode, in and out of
+    place, both directions, against the oracle; nothing past the data is
+    written."""
+    batch = fb.Batch(lens, n2d=n2d, side2d=3)
+    x = packed_input(batch, 23)
+    e = batch.elements
+    ws = torch.zeros(8 * e + 512, dtype=torch.uint8, device="cuda")
+    wsp = (ws.data_ptr() + 255) // 256 * 256
+    for direction in (fb.FB_FORWARD, fb.FB_INVERSE):
+        ref = np.concatenate([ref_transform(batch, x, i, direction) for i in range(len(lens) + n2d)])
+        for in_place in (False, True):
+            for persistent in MODES:
+                print(f"odd side lens={len(lens)} n2d={n2d} dir={direction} in_place={in_place} mode={persistent}",
+                      flush=True)
+                buf = torch.full((e + 64,), 7.0, dtype=torch.complex64, device="cuda")
+                buf[:e] = torch.from_numpy(x)
+                src = buf[:e]
+                dst = src if in_place else torch.full((e + 64,), 7.0, dtype=torch.complex64, device="cuda")[:e]
+                fb.fb_batch_exec(batch, src, dst, wsp, direction, persistent)
+                assert rel_l2(dst.cpu().numpy().astype(np.complex128), ref) < TOL
+                whole = torch.as_strided(dst, (e + 64,), (1,))
+                assert torch.all(whole[e:] == 7.0)
