@@ -123,10 +123,13 @@ template <typename V, int N, bool CONTIG, bool MX = false, bool MULTI = false, b
     }
     // ... and of a multi-output pass: long complex64 tiles of 2^a points ask for 56 KB, two
     // on a CU (with the three or four that their registers allow, 5 steps of
-    // 32 x 64 x 1024 took 98.6 us instead of 89.3, 2048 points 98.0 instead of 88.1)
+    // 32 x 64 x 1024 took 98.6 us instead of 89.3, 2048 points 98.0 instead of
+    // 88.1).  Not the matrix-core tiles, of half the threads: two on a CU are one
+    // wavefront per SIMD (5 steps of split-bf16 512 points on 16 MiB 110 us, 96
+    // with four on a CU; 1024 and 2048 points 1.01 and 0.99 of that)
     static constexpr int lds_elems_multi()
     {
-        const int floor = sizeof(V) == 8 && N >= 512 && N % 3 != 0 ? 56 * 1024 / 8 : 0;
+        const int floor = sizeof(V) == 8 && !MX && N >= 512 && N % 3 != 0 ? 56 * 1024 / 8 : 0;
         return P * LS > floor ? P * LS : floor;
     }
     static constexpr int LIN = (N + T - 1) / T;   // elements per thread of a tile moved as one block
@@ -941,7 +944,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs &a, int64_t tile, int t
                     // exchange: write the previous stage's outputs
                     constexpr int Rp = GP.g[s - 1];
                     constexpr int Nsp = GP.ns[s - 1];
-                constexpr bool G0P = Nsp == 1 && Rp == 16;   // a butterfly's outputs are one group of 16
+                    constexpr bool G0P = Nsp == 1 && Rp == 16;   // a butterfly's outputs are one group of 16
                     constexpr int NBFp = N / Rp;
                     constexpr int Up = (NBFp + T - 1) / T;
 #pragma unroll
