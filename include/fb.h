@@ -200,7 +200,8 @@ fb_status fb_fft3d_forward_uniform(const fb_plan *p, uint64_t seed, void *out, v
  * strictly lower part holds L (unit diagonal, not stored) and the upper part
  * U, with P a = L U where P applies, for j = 0..n-1 in order, the swap of
  * rows j and ipiv[j] (0-based, ipiv[j] >= j).  The pivot of column j is the
- * first row of largest magnitude.  info (device) receives 0, or j + 1 for
+ * first row of largest magnitude, a NaN counting as larger than any number.
+ * L's entries are correctly rounded quotients.  info (device) receives 0, or j + 1 for
  * the first column j whose pivot is zero (the factorization still
  * completes, as the usual library convention).  ipiv (n int32) and info are
  * device memory owned by the caller; nothing is allocated.  1 <= n <= 2048

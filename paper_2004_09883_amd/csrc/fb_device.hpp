@@ -30,7 +30,8 @@ template <typename V> __device__ __forceinline__ V cadd(V a, V b) { return mk<V>
 template <typename V> __device__ __forceinline__ V csub(V a, V b) { return mk<V>(a.x - b.x, a.y - b.y); }
 // The products are fused by hand: left to the compiler, which of the two
 // products of a sum is the rounded one depends on the code around it, and the
-// same pass compiled into two kernels would not give the same bits.
+// same pass compiled into two kernels would not give the same bits.  (The
+// matrix-core stages' twiddle products are not: mx_cmul in fb_mfma.hpp.)
 __device__ __forceinline__ double fused(double a, double b, double c) { return fma(a, b, c); }
 __device__ __forceinline__ float fused(float a, float b, float c) { return fmaf(a, b, c); }
 template <typename V> __device__ __forceinline__ V cmul(V a, V b)

@@ -29,12 +29,16 @@
 
 namespace fb {
 
-// a * b ahead of the split into bf16 parts, fused as the compiler chooses
+// a * b ahead of the split into bf16 parts.  Which of its products are fused is
+// the compiler's choice, unlike in cmul: it differs between the elements of one
+// stage (written out, none of the four forms gives the results of 48, 256, 768,
+// 1536 or 4096 points), and the products' last bit is far below what the split
+// keeps.  So that passes with one output and with several agree is not given by
+// the source; a test holds every length to it.
 __device__ __forceinline__ float2 mx_cmul(float2 a, float2 b)
 {
     return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
-
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -129,7 +133,9 @@ __device__ __forceinline__ void mx_stage16(const float2 *__restrict__ tw, const 
             const int q = 4 * g + i;
             float2 v = src.load(h, b + q * NBF);
             if constexpr (Ns > 1) {
-                // (each form where it keeps the results that the stage always had)
+                // (cmul where it gives the results that the compiler's choice
+                // gave before the vector stages were fused by hand, mx_cmul
+                // elsewhere; neither is the better product)
                 if (q > 0) {
                     const float2 w = tw[TWOFF + (q - 1) * Ns + (b % Ns)];
                     constexpr int LAST = radix_plan(N).r[radix_plan(N).count - 1];

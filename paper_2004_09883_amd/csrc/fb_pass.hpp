@@ -125,7 +125,7 @@ template <typename V, int N, bool CONTIG, bool MX = false, bool MULTI = false, b
     // on a CU (with the three or four that their registers allow, 5 steps of
     // 32 x 64 x 1024 took 98.6 us instead of 89.3, 2048 points 98.0 instead of
     // 88.1).  Not the matrix-core tiles, of half the threads: two on a CU are one
-    // wavefront per SIMD (5 steps of split-bf16 512 points on 16 MiB 110 us, 96
+    // wavefront per SIMD (5 steps of split-bf16 512 points on 16 MiB 108 us, 94
     // with four on a CU; 1024 and 2048 points 1.01 and 0.99 of that)
     static constexpr int lds_elems_multi()
     {

@@ -680,3 +680,19 @@ def test_exec_host_equals_device_exec(dtype):
         y = x.copy()
         fb.fb_fft3d_exec_host(plan, y, y, direction)
         assert np.array_equal(y, want)
+
+
+@pytest.mark.parametrize("nz", [n for n in LENGTHS + LENGTHS_3B if n % 16 == 0])
+def test_split_bf16_steps_from_one_read_equal_single_steps(nz):
+    """The z pass with several outputs and the single one are two compilations
+    of the same matrix-core stages; the contraction of their twiddle products
+    is the compiler's choice, and has to be the same one in both."""
+    shape = (3, 1, nz)
+    plan = fb.Plan(*shape, fb.FB_C64_SPLITBF16)
+    u = dev(inputs.uniform_grid(shape, nz), fb.FB_C64_SPLITBF16)
+    multi = torch.full((3,) + shape, 3.0, dtype=plan.torch_dtype, device="cuda")
+    one = torch.empty(shape, dtype=plan.torch_dtype, device="cuda")
+    fb.fb_spectral_steps(plan, u, multi, 1e-4, [1.0, 2.0, 3.0])
+    for j in range(3):
+        fb.fb_spectral_step(plan, u, one, 1e-4, j + 1.0)
+        assert torch.equal(one, multi[j]), j
