@@ -323,7 +323,8 @@ constexpr int grouped_pencils(int n, int threads, bool contig, int esize, bool s
 //    1.8 at any size;
 //  - cached passes with several outputs, which store more than they load: 5 steps
 //    as a whole 0.92 to 1.0 from 512 (complex128, up to 18 points; longer ones 1.0
-//    to 1.08) and 1024 (complex64, 0.93 to 1.0).
+//    to 1.08) and 1024 (complex64, 0.93 to 1.0; 9, 18 and 36 points 0.94 to 0.99
+//    from 512).
 constexpr int block_waves(int n, int esize, bool one_group, bool nt, bool multi)
 {
     if (esize == 16) {
@@ -337,7 +338,7 @@ constexpr int block_waves(int n, int esize, bool one_group, bool nt, bool multi)
     if (nt && n <= 48) return n <= 3 ? 0 : n == 4 ? 4096 : n <= 16 ? 1024 : multi && n == 27 ? 256 : 512;
     if (nt) return n <= 72 || n == 96 ? 768 : n <= 243 ? 1536 : 4096;
     if (n <= 4 || n > 48) return 0;
-    if (multi) return 1024;
+    if (multi) return n == 9 || n == 18 || n == 36 ? 512 : 1024;
     return n == 27 ? 0 : n == 18 ? 4096 : n == 16 || n == 32 ? 1024 : 2048;
 }
 
